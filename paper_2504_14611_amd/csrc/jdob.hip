@@ -16,8 +16,8 @@
 //   4. a wavefront argmin with lowest-index ties, the winner's per-user
 //      levels, the canonical energy sum and the release time (Eq. (22)).
 //
-// Two facts let the kernel skip work without changing the result (both
-// follow from the rounding of each operation being monotone):
+// Three facts let the kernel skip work without changing the result (the
+// first two follow from the rounding of each operation being monotone):
 //   * for fixed (s, j) the feasible batches are an interval [max(bmin,1),
 //     bmax], and bmax grows with the GPU frequency (the monotone thresholds
 //     of Eq. (18)): a pass over b with no feasible lane ends the partition
@@ -25,7 +25,14 @@
 //     the partition point has any feasible candidate at all;
 //   * inside a candidate the budget H - up[i] shrinks along pi, so the
 //     offloaders' levels never decrease: each lane advances its level
-//     instead of searching it per user.
+//     instead of searching it per user;
+//   * a candidate's energy is a sum of non-negative terms with cheap lower
+//     bounds: partition points, batches and candidates whose bound exceeds
+//     the energy of local computing or of a candidate found before can
+//     neither win nor tie (see beaten).  Searched best bound first, few are
+//     left: 1,048,576 instances of 32 users, 22 layers 9.5 -> 1.55 ms, 65,537
+//     of 128 users, 50 layers 12.5 -> 1.09 ms, the grouping of 65,536
+//     instances of 10 users 22.7 -> 4.8 ms.
 // The kernel is a VALU/LDS-bound loop of compares, selects and adds: it is
 // not a dense contraction and uses no matrix cores.
 
@@ -479,6 +486,100 @@ __device__ inline int wave_sum_int(int v) {
   return lane_read(v, WAVE - 1);
 }
 
+// Energy bounds.  A candidate's ranking energy is a sum of non-negative terms,
+// so a sum with every term replaced by a lower bound of it cannot exceed it by
+// more than rounding: at most about 2 N roundings of 2^-24 (binary32, N <=
+// 1024: 1.2e-4, and the hardware reciprocals' ulps).  A bound that exceeds the
+// energy of some candidate (inc) by 2^-12 of itself therefore belongs to
+// candidates that neither win nor tie: they need not be evaluated.
+template <typename T> __device__ inline bool beaten(T lb, T inc) {
+  return lb * T(1.0 - 0x1p-12) > inc;
+}
+
+// Hardware reciprocal, for bounds.
+__device__ inline float rough_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ inline double rough_rcp(double x) { return __builtin_amdgcn_rcp(x); }
+
+// A little less than 1 / x (x > 0; the hardware's reciprocal of a denormal is
+// infinite).
+__device__ inline float rcp_below(float x) {
+  const float q = rough_rcp(x) * (1.0f - 0x1p-20f);
+  return q < 0x1p126f ? q : 0x1p126f;
+}
+__device__ inline double rcp_below(double x) {
+  const double q = rough_rcp(x) * (1.0 - 0x1p-20);
+  return q < 0x1p1022 ? q : 0x1p1022;
+}
+
+// CPU energy kC * f^2 (kC = kappa * C[s]) of a user with budget x or less, from
+// below: the lowest frequency finishing Cs cycles by then, at least f0 (also
+// where x <= 0 or Cs = 0 makes the quotient negative or NaN).
+template <typename T> __device__ inline T least_cpu(T Cs, T kC, T x, T f0) {
+  const T q = Cs * rough_rcp(x);
+  const T f = q > f0 ? q : f0;
+  return kC * (f * f);
+}
+
+// Lowest GPU energy per second of batch latency at the top level, over the
+// GPU levels searched: P_j * Phi_j >= rho * (A[s] + B[s]*b).
+template <typename T>
+__device__ inline T gpu_energy_rate(const Problem<T> &p, const unsigned char *smem, const Layout &y,
+                                    int lane) {
+  const T *sr = (const T *)(smem + y.r), *sP = (const T *)(smem + y.P);
+  T v = inf_of<T>();
+  for (int j = p.j_low + lane; j < p.J; j += WAVE) {
+    const T e = sP[j] * sr[j];
+    v = e < v ? e : v;
+  }
+  return wave_min(v);
+}
+
+// Base-2 logarithm of the lanes that one of n items can have when the wave
+// takes up to 64 items at once.
+__device__ inline int lanes_per_item(int n) {
+  return n >= WAVE ? 0 : (n > 1 ? __clz(n - 1) - 26 : 6);
+}
+
+// With local computing feasible, drops the flag of every partition point s
+// whose candidates cannot beat it: each user costs at least the lower of its
+// local energy and that of offloading at the lowest CPU level plus its share
+// rho*B[s] of the batch, on top of rho*A[s].  Lanes take (s, part of the
+// users): two operations per (s, user), against the sort, the scans and the
+// rows that an instance ending here does without (1,048,576 instances of 32
+// users, 22 layers: a flag is left in 3 % of them, of 59 % flagged).
+// Returns whether a flag is left.
+template <typename T>
+__device__ inline bool drop_beaten(const Problem<T> &p, unsigned char *smem, const Layout &y,
+                                   int lane) {
+  const int N = p.N;
+  const T *sC = (const T *)(smem + y.C), *sA = (const T *)(smem + y.A);
+  const T *sB = (const T *)(smem + y.B), *seps = (const T *)(smem + y.eps);
+  const T *seL = (const T *)(smem + y.eL);
+  int8_t *sflag = (int8_t *)(smem + y.sflag);
+  const T rho = gpu_energy_rate(p, smem, y, lane);
+  T lc = T(0);
+  for (int m = lane; m < N; m += WAVE) lc = lc + seL[m];
+  lc = lane_read(wave_iscan(lc, T(0), [](T a, T b) { return a + b; }), WAVE - 1);
+  const int lg = lanes_per_item(p.s_end), parts = 1 << lg, part = lane & (parts - 1);
+  bool left = false;
+  for (int s0 = 0; s0 < p.s_end; s0 += WAVE >> lg) {
+    const int s = s0 + (lane >> lg);
+    const int sc = s < p.s_end ? s : 0;
+    const T off = fma_(rho, sB[sc], seps[0] * sC[sc]);
+    T acc = T(0);
+    for (int m = part; m < N; m += parts) {
+      const T e = seL[m];
+      acc = acc + (e < off ? e : off);
+    }
+    acc = run_reduce(acc, lg, [](T a, T b) { return a + b; });
+    if (s < p.s_end) {
+      if (beaten(fma_(rho, sA[sc], acc), lc)) sflag[s] = 0;  // (its lanes agree)
+      left |= sflag[s] != 0;
+    }
+  }
+  return __builtin_amdgcn_ballot_w64(left) != 0;
+}
+
 // Preparation of the fused solve.  Every step is exact (orders, minima and
 // the tests of the contract), so the candidate search only runs where it can
 // find something:
@@ -494,8 +595,11 @@ __device__ inline int wave_sum_int(int v) {
 //   4. only if some partition point passes: the rate order pi, the batch
 //      deadlines lo[b], the rates in pi order and the local-energy suffix
 //      sums SL that the search reads.
-// Returns whether some partition point passed; bmin_out receives bmin.
-template <typename T, bool CONT>
+//   (unless KEEP) when local computing is feasible, the passing partition
+//   points whose energy bound exceeds its energy are dropped first (see
+//   drop_beaten): most instances where it wins end here, unsorted.
+// Returns whether some partition point is left; bmin_out receives bmin.
+template <typename T, bool CONT, bool KEEP>
 __device__ bool prepare_fused(const Problem<T> &p, int64_t inst, unsigned char *smem,
                               const Layout &y, int lane, T tfree, int &bmin_out) {
   const int N = p.N, L = p.L, K = p.K, J = p.J;
@@ -651,7 +755,12 @@ __device__ bool prepare_fused(const Problem<T> &p, int64_t inst, unsigned char *
     }
   }
   bmin_out = bmin;
-  if (!__builtin_amdgcn_ballot_w64(any != 0)) {
+  bool left = __builtin_amdgcn_ballot_w64(any != 0) != 0;
+  if (!KEEP && left && bmin == 0) {
+    __syncthreads();  // the flags and local energies, read by other lanes
+    left = drop_beaten(p, smem, y, lane);
+  }
+  if (!left) {
     if (bmin == 0) {  // local computing is the only candidate: its ranking energy
       T e = T(0);
       for (int m = lane; m < N; m += WAVE) e = e + seL[m];
@@ -787,8 +896,8 @@ template <typename T, bool FROM_TABLES, bool ONE_CHUNK, bool COUNT, bool GREEDY,
           bool QUEUE>
 __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &tab, int64_t inst,
                                          unsigned char *smem, const Layout &y, int lane, int N,
-                                         int blo, T tfree, T &bestE, int &bestI, int &nfeas,
-                                         int &nevals, bool flags_ready = false) {
+                                         int blo, T tfree, T inc, T rho, T &bestE, int &bestI,
+                                         int &nfeas, int &nevals, bool flags_ready = false) {
   const int L = p.L, K = p.K, J = p.J;
   const int s_end = p.s_end, j_low = p.j_low;
   T *sC = (T *)(smem + y.C), *sA = (T *)(smem + y.A), *sB = (T *)(smem + y.B);
@@ -805,24 +914,6 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
   const int KR = level_row_len(K);
   const bool fuse_div = !FROM_TABLES && N + KR <= WAVE;
 
-
-  // Which partition points have any feasible candidate: the test at the top
-  // GPU level and the smallest admissible batch (same operations as below;
-  // the fused solve has run it during its preparation).
-  if (!flags_ready) {
-    for (int s = lane; s < s_end; s += WAVE) {
-      int ok = 0;
-      if (blo <= N) {
-        const T tK1 = sC[s] / sf[K - 1];
-        const T upl = upload_time<T, FROM_TABLES>(p, tab, inst, sbits, srate, spi, s, blo - 1);
-        const T Phi = (sA[s] + sB[s] * T(blo)) * sr[J - 1];
-        const T H = slo[blo] - Phi;
-        ok = (H >= tfree) && (tK1 <= H - upl);
-      }
-      sflag[s] = ok;
-    }
-    __syncthreads();
-  }
 
   // lane -> (j, b) inside a pass: j = j_low + jl fastest, nb batch sizes per
   // pass.  Lanes beyond nb*Jw (Jn not dividing 64) stay idle.
@@ -842,16 +933,8 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
   const T rj1 = sr[j1], pj1 = sP[j1];
   const uint64_t jokm = __builtin_amdgcn_ballot_w64(!idle);  // lanes holding a candidate
 
-  // batch records past N are infeasible sentinels (lo = -inf)
-  for (int q = lane; q < batch_sentinels(Jn, GREEDY); q += WAVE) {
-    Batch<T> z;
-    z.lo = -inf_of<T>();
-    z.upl = T(0);
-    z.esl = T(0);
-    z.ab = T(0);
-    sbt[N + 1 + q] = z;
-  }
-
+  // for the bounds (see beaten)
+  const T rtop = uni(sr[J - 1]), ftop = uni(sf[K - 1]), f0 = uni(sf[0]);
 
   // Eq. (20) per offloader: the budget shrinks along pi, so a lane's level
   // only moves up.  The CPU part of Eq. (21) is summed by runs of equal
@@ -883,6 +966,23 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
       mv = tk > x;                                             \
     }                                                          \
   }
+
+  // inc, the lowest energy of a candidate known, after lanes with `take` found E
+  auto lower_inc = [&](bool take, T E) {
+    if (__builtin_amdgcn_ballot_w64(take & (E < inc))) {
+      const T m = wave_min(take ? E : inf_of<T>());
+      inc = m < inc ? m : inc;
+    }
+  };
+
+  // Partition points come in no fixed order: the flat index breaks ties (an
+  // infinite energy never wins).
+  auto merge = [&](T bE, int bI) {
+    if ((bE < bestE) | ((bE == bestE) & (bE < inf_of<T>()) & (bI < bestI))) {
+      bestE = bE;
+      bestI = bI;
+    }
+  };
 
   // Row s into (up_, bt_, te_): Eq. (1), (2) per level (-inf sentinels past
   // the last level stop the level searches), Eq. (3) per user, and per batch size b the
@@ -1024,56 +1124,42 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
     const bool take = feas & better(E, idx, bE, bI);
     bE = take ? E : bE;
     bI = take ? idx : bI;
-    if (COUNT) {
-      nfeas += feas ? 1 : 0;
-      nevals += feas ? b : 0;
-    }
   };
 
-  if constexpr (GREEDY && !CONT) {
-    // Alg. 2 needs one lane per GPU level.  When the searched levels fit half
-    // a wave, lanes [0, 32) take one flagged partition point and lanes
-    // [32, 64) the next, the second set of rows in the room of the batch
-    // sentinels (this family reads no record past N + 1, so the sentinel at
-    // N + 1 of both sets is all it needs).
-    const int half = WAVE / 2;
-    if (Jn <= half && 8 * (N + 2) + ((N + 3) & ~3) + 8 + 2 * KR <= 4 * (N + 2 + WAVE)) {
-      Batch<T> *bt2 = sbt + N + 2;  // its record N + 1 is sentinel N + 1 + (N + 2) <= N + 65
-      T *up2 = (T *)(bt2 + N + 2);
-      Level<T> *te2 = (Level<T> *)(up2 + ((N + 3) & ~3) + 8);
-      const bool hi = lane >= half;
-      const int j = j_low + lane - (hi ? half : 0);
-      int s = 0;
-      while (s < s_end && !uni(sflag[s])) ++s;
-      while (s < s_end) {
-        int s2 = s + 1;
-        while (s2 < s_end && !uni(sflag[s2])) ++s2;
-        build_row(s, sup, sbt, ste);
-        if (s2 < s_end) build_row(s2, up2, bt2, te2);
-        __syncthreads();
-        T bE = inf_of<T>();
-        int bI = 0x7fffffff;
-        const bool jok = j < J && (!hi || s2 < s_end);
-        greedy_at(hi ? s2 : s, j, jok, hi ? up2 : sup, hi ? bt2 : sbt, hi ? te2 : ste, bE, bI);
-        // each lane meets its partition points in increasing order
-        if (bE < bestE) { bestE = bE; bestI = bI; }
-        __syncthreads();
-        s = s2 + 1;
-        while (s < s_end && !uni(sflag[s])) ++s;
-      }
-      return;
-    }
-  }
+  // Alg. 2 needs one lane per GPU level.  When the searched levels fit half
+  // a wave, lanes [0, 32) take one partition point and lanes [32, 64) the
+  // next, the second set of rows in the room of the batch sentinels (this
+  // family reads no record past N + 1, so the sentinel at N + 1 of both sets
+  // is all it needs).
+  constexpr int half = WAVE / 2;
+  const bool halves = GREEDY && !CONT && Jn <= half &&
+                      8 * (N + 2) + ((N + 3) & ~3) + 8 + 2 * KR <= 4 * (N + 2 + WAVE);
+  auto greedy_rows = [&](int s, int s2) {
+    Batch<T> *bt2 = sbt + N + 2;  // its record N + 1 is sentinel N + 1 + (N + 2) <= N + 65
+    T *up2 = (T *)(bt2 + N + 2);
+    Level<T> *te2 = (Level<T> *)(up2 + ((N + 3) & ~3) + 8);
+    const bool hi = lane >= half;
+    const int j = j_low + lane - (hi ? half : 0);
+    build_row(s, sup, sbt, ste);
+    if (s2 >= 0) build_row(s2, up2, bt2, te2);
+    __syncthreads();
+    T bE = inf_of<T>();
+    int bI = 0x7fffffff;
+    const bool jok = j < J && (!hi || s2 >= 0);
+    greedy_at(hi ? s2 : s, j, jok, hi ? up2 : sup, hi ? bt2 : sbt, hi ? te2 : ste, bE, bI);
+    merge(bE, bI);
+    __syncthreads();
+  };
 
-  for (int s = 0; s < s_end; ++s) {
-    if (!uni(sflag[s])) continue;
+  // Candidates of partition point s, in its rows.
+  auto search_row = [&](int s) {
     build_row(s, sup, sbt, ste);
     __syncthreads();
     const T Cs = uni(sC[s]);
     const T tK1 = uni(ste[K - 1].t);
     const int sJN = s * J * N;
     // continuous CPU frequency: kappa * C[s] and the frequency range
-    const T kC = CONT ? p.kappa * Cs : T(0);
+    const T kC = p.kappa * Cs;
     const T fmin = CONT ? uni(sf[0]) : T(0), fmax = CONT ? uni(sf[K - 1]) : T(0);
 
     T bE = inf_of<T>();  // best of this lane within partition point s
@@ -1145,9 +1231,30 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
       qE = take ? E : qE;
       qI = take ? idx : qI;
       qhead += cnt;
+      lower_inc(take, E);
     };
-    for (int b0 = blo; b0 <= N; b0 += nb) {
-      bool any = false;
+    int c0 = blo;
+    while (c0 <= N) {
+      // Batch sizes c0 .. c0 + 63 worth a pass, lane = b: feasible at the top
+      // GPU level (the feasible ones are a prefix) and not beaten by inc with
+      // the least GPU energy and with every offloader at the lowest frequency
+      // that the first one, whose budget is the largest, can run at.
+      uint64_t todo;
+      {
+        const int b = c0 + lane;
+        const Batch<T> r = sbt[b <= N ? b : N + 1];
+        const T H = r.lo - r.ab * rtop;
+        const bool ok = (b <= N) & (H >= tfree) & (tK1 <= H - r.upl);
+        const T lb = fma_(T(b), least_cpu(Cs, kC, H - up0, f0), fma_(rho, r.ab, r.esl));
+        const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
+        if (okm == 0) break;
+        todo = okm & ~__builtin_amdgcn_ballot_w64(beaten(lb, inc));
+      }
+      int next = c0 + WAVE;
+      while (todo) {
+      const int b0 = c0 + __builtin_ctzll(todo);
+      next = b0 + nb > next ? b0 + nb : next;
+      todo = b0 + nb - c0 < WAVE ? todo & (~uint64_t(0) << (b0 + nb - c0)) : 0;
       for (int jc = 0; jc < (ONE_CHUNK ? WAVE : Jn); jc += WAVE) {
         const int j = j_low + jc + jl;
         const bool jok = one_chunk ? !idle : j < J;
@@ -1161,16 +1268,22 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
         const uint64_t mask = __builtin_amdgcn_ballot_w64(c6) & __builtin_amdgcn_ballot_w64(c7) &
                               (one_chunk ? jokm : __builtin_amdgcn_ballot_w64(jok));
         if (mask == 0) continue;
-        any = true;
         const int b = b0 + bo;
+        const T bar = inc < bE ? inc : bE;  // an energy to beat
         T E;
-        bool multi = false;  // queued: evaluated by flush
+        bool valid = feas;   // E is the candidate's energy
         if constexpr (CONT) {
-          const int hi = 63 - __clzll((long long)mask);
-          const int bpass = b0 + __builtin_amdgcn_readlane(bo, hi);  // largest feasible b
+          // with every offloader at the first one's frequency, the lowest
+          const T pj = one_chunk ? pj1 : sP[jok ? j : 0];
+          const T lb = fma_(pj, Phi, fma_(T(b), least_cpu(Cs, kC, H - up0, f0), r.esl));
+          const uint64_t need = mask & ~__builtin_amdgcn_ballot_w64(beaten(lb, bar));
+          if (need == 0) continue;
+          valid = feas & !beaten(lb, bar);
+          const int hi = 63 - __clzll((long long)need);
+          const int bpass = b0 + __builtin_amdgcn_readlane(bo, hi);  // largest b needed
           const T Hu = feas ? H : inf_of<T>();
           const T f2 = (Cs > T(0)) ? cont_sum_f2(sup, Hu, b, b0, bpass, Cs, fmin, fmax) : T(0);
-          E = fma_(one_chunk ? pj1 : sP[jok ? j : 0], Phi, fma_(kC, f2, r.esl));
+          E = fma_(pj, Phi, fma_(kC, f2, r.esl));
         } else {
           // Eq. (20) for the first offloader: the number of levels too slow
           // for its budget (latency falls with the level), by steps up from
@@ -1197,8 +1310,11 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
           // When the last offloader fits the first one's level, every
           // offloader runs at it (the levels rise along pi): b of its energy.
           E = fma_(one_chunk ? pj1 : sP[jok ? j : 0], Phi, T(b) * q0.e + r.esl);
+          // Otherwise that is a bound: the others' levels are higher.
           const bool up_last = q0.t > hl;
-          const uint64_t mm = mask & __builtin_amdgcn_ballot_w64(up_last);
+          valid = feas & !up_last;
+          const bool open = up_last & !beaten(E, bar);
+          const uint64_t mm = mask & __builtin_amdgcn_ballot_w64(open);
           if (!QUEUE && mm) {
             // Otherwise, in short batches, the CPU part of Eq. (21) by runs
             // of equal level: a walk over the users, four per broadcast read
@@ -1206,7 +1322,7 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
             // that fits its last offloader.  Users below b0 belong to every
             // lane's batch; past a lane's batch the budget is +inf.  The
             // other lanes get an infinite budget and drop the result.
-            const bool walk = feas & up_last;
+            const bool walk = feas & open;
             const T Hm = walk ? H : inf_of<T>();
             const T hm = walk ? hl : inf_of<T>();
             const int bw = b0 + __builtin_amdgcn_readlane(bo, 63 - __clzll((long long)mm));
@@ -1232,9 +1348,10 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
             acc = fma_(T(b - run), lv->e, acc);
             const T Ew = fma_(one_chunk ? pj1 : sP[jok ? j : 0], Phi, acc + r.esl);
             E = walk ? Ew : E;
+            valid |= walk;
           } else if (QUEUE && mm) {
             // the candidate joins the queue
-            multi = feas & up_last;
+            const bool multi = feas & open;
             const int slot = qtail + (int)__builtin_amdgcn_mbcnt_hi(
                                          (uint32_t)(mm >> 32),
                                          __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u));
@@ -1246,29 +1363,160 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
           }
         }
         if (one_chunk) {
-          const bool take = feas & !(QUEUE && multi) & (E <= bE);
+          const bool take = valid & (E <= bE);
           bE = take ? E : bE;
           bI = take ? b : bI;
+          lower_inc(take, E);
         } else {
           const int idx = sJN + (J - 1 - j) * N + (N - b);
-          const bool take = feas & !(QUEUE && multi) & better(E, idx, bE, bI);
+          const bool take = valid & better(E, idx, bE, bI);
           bE = take ? E : bE;
           bI = take ? idx : bI;
-        }
-        if (COUNT) {
-          nfeas += feas ? 1 : 0;
-          nevals += feas ? b : 0;
+          lower_inc(take, E);
         }
       }
-      if (!any) break;
+      }
+      c0 = next;
     }
     if (QUEUE && qtail > qhead) flush(qtail - qhead);
     if (one_chunk && bI != 0x7fffffff) bI = sJN + (J - 1 - j1) * N + (N - bI);
     if (QUEUE && better(qE, qI, bE, bI)) { bE = qE; bI = qI; }
     }
-    // later partition points have higher flat indices: strict "<" merges
-    if (bE < bestE) { bestE = bE; bestI = bI; }
+    merge(bE, bI);
     __syncthreads();
+  };
+
+  if constexpr (COUNT && GREEDY) {
+    // The work counters of the greedy family: the batch of each (s, j), found
+    // by binary search over b with the test (7), if it meets the others.
+    // Lanes take (s, j) pairs, several partition points at once where J leaves
+    // room.
+    const int lg = 6 - lanes_per_item(Jn), jq = lane & ((1 << lg) - 1);
+    for (int s0 = 0; s0 < s_end; s0 += WAVE >> lg) {
+      const int s = s0 + (lane >> lg);
+      const bool in = s < s_end && (!flags_ready || sflag[s]);
+      if (!__builtin_amdgcn_ballot_w64(in)) continue;
+      const int sc = in ? s : 0;
+      const T tK1 = sC[sc] / ftop, As = sA[sc], Bs = sB[sc];
+      for (int jc = j_low; jc < J; jc += 1 << lg) {
+        const bool act = in && jc + jq < J;
+        const T rj = sr[act ? jc + jq : J - 1];
+        auto slack = [&](int b) { return slo[b] - (As + Bs * T(b)) * rj; };
+        int bg = 0;
+        for (int step = top; step > 0; step >>= 1) {
+          const int c = bg + step, cc = c <= N ? c : N;
+          const T up = upload_time<T, FROM_TABLES>(p, tab, inst, sbits, srate, spi, sc, cc - 1);
+          bg = (c <= N && tK1 <= slack(cc) - up) ? c : bg;
+        }
+        if (act && bg >= blo && slack(bg) >= tfree) {
+          nfeas += 1;
+          nevals += bg;
+        }
+      }
+    }
+  }
+
+  // Partition points by their lowest bound, until it is beaten by the best
+  // energy found: the winner's is usually among the first (10 users in a
+  // group: 22 partition points hold feasible candidates, 1.5 are searched; 32
+  // users: 13 and 0.1; 128 users: 14 and 7).  A partition point's bound is the
+  // least over b of: the least GPU energy, the upload energy of the first b
+  // users, the local energy of the others, and b users' CPU energy at the
+  // lowest frequency that the first user, whose budget is the largest, can run
+  // at.  Lanes take (s, part of the batch sizes).  Upload latencies enter by
+  // reciprocal rates, rounded down (not at all when they come from tables).
+  // The per-b inputs {lo[b], SL[b], sum and last of the reciprocal rates of
+  // the first b} share the room of the batch records.
+  // One or two partition points are searched as they come.  The grid's work
+  // counters come from the same walk over (s, b): the feasible GPU levels are
+  // the highest ones, down to a level found by binary search with the tests of
+  // the passes.
+  const int jtop = 1 << (31 - __clz(Jn));
+  for (int s0 = 0; s0 < s_end; s0 += WAVE) {
+    uint64_t open = __builtin_amdgcn_ballot_w64(s0 + lane < s_end &&
+                                                (!flags_ready || sflag[s0 + lane]));
+    const bool bounds = (open & (open - 1) & ((open & (open - 1)) - 1)) != 0;  // three or more
+    T lb = inf_of<T>();
+    const int lg = lanes_per_item(s_end), parts = 1 << lg, part = lane & (parts - 1);
+    if (bounds || (COUNT && !GREEDY && open)) {
+      T carry = T(0);
+      for (int i0 = 0; i0 < N; i0 += WAVE) {
+        const int i = i0 + lane;
+        const T rr = (!FROM_TABLES && i < N) ? rcp_below(srate[i]) : T(0);
+        const T w = FROM_TABLES ? T(0) : scan_add(rr) + carry;
+        if (i < N) {
+          Batch<T> r;
+          r.lo = slo[i + 1];
+          r.esl = sSL[i + 1];
+          r.ab = w;
+          r.upl = rr;
+          sbt[i + 1] = r;
+        }
+        carry = lane_read(w, WAVE - 1);
+      }
+      __syncthreads();
+      const int s = s0 + (lane >> lg);
+      const int sc = s < s_end ? s : 0;
+      const T Cs = sC[sc], As = sA[sc], Bs = sB[sc], kC = p.kappa * Cs, tmin = Cs / ftop;
+      const T Os = FROM_TABLES ? T(0) : sbits[sc], pO = p.ptx * Os;
+      const T up0 = FROM_TABLES ? T(0) : Os * sbt[1].upl;
+      for (int b = blo + part; b <= N; b += parts) {
+        const Batch<T> r = sbt[b];
+        const T ab = As + Bs * T(b), H = r.lo - ab * rtop;
+        const bool ok = (H >= tfree) & (tmin <= H - Os * r.upl);
+        const T e = fma_(T(b), least_cpu(Cs, kC, H - up0, f0), fma_(rho, ab, fma_(pO, r.ab, r.esl)));
+        lb = (ok & (e < lb)) ? e : lb;
+        if constexpr (COUNT && !GREEDY) {
+          const T up = upload_time<T, FROM_TABLES>(p, tab, inst, sbits, srate, spi, sc, b - 1);
+          int low = 0;  // levels that miss a deadline
+          for (int step = jtop; step > 0; step >>= 1) {
+            const int c = low + step;
+            const T Hj = r.lo - ab * sr[c <= Jn ? j_low + c - 1 : J - 1];
+            low = (c <= Jn && !(Hj >= tfree && tmin <= Hj - up)) ? c : low;
+          }
+          if ((open >> (lane >> lg)) & 1) {
+            nfeas += Jn - low;
+            nevals += (Jn - low) * b;
+          }
+        }
+      }
+      lb = run_reduce(lb, lg, [](T a, T b) { return b < a ? b : a; });
+      if (!((open >> (lane >> lg)) & 1)) lb = inf_of<T>();
+      __syncthreads();
+    }
+    // batch records past N are infeasible sentinels (lo = -inf)
+    for (int q = lane; q < batch_sentinels(Jn, GREEDY); q += WAVE) {
+      Batch<T> z;
+      z.lo = -inf_of<T>();
+      z.upl = T(0);
+      z.esl = T(0);
+      z.ab = T(0);
+      sbt[N + 1 + q] = z;
+    }
+    // the next partition point, -1 if none left can win
+    auto pop = [&]() -> int {
+      if (!bounds) {
+        if (!open) return -1;
+        const int q = __builtin_ctzll(open);
+        open &= open - 1;
+        return s0 + q;
+      }
+      const T m = wave_min(lb);
+      if (!(m < inf_of<T>()) || beaten(m, inc)) return -1;
+      const int q = __builtin_ctzll(__builtin_amdgcn_ballot_w64(lb == m)) >> lg;
+      lb = (lane >> lg) == q ? inf_of<T>() : lb;
+      return s0 + q;
+    };
+    for (int s1 = pop(); s1 >= 0; s1 = pop()) {
+      if (halves)
+        greedy_rows(s1, pop());
+      else
+        search_row(s1);
+      if (GREEDY && bounds) {
+        const T m = wave_min(bestE);
+        inc = m < inc ? m : inc;
+      }
+    }
   }
 #undef JDOB_USER
 #undef JDOB_USER0
@@ -1298,7 +1546,7 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_solve_kernel(SolveArgs<T> args) 
   if (FROM_TABLES)
     prepare_instance<T, FROM_TABLES, CONT>(p, tab, inst, smem, y, lane, bmin);
   else
-    any = prepare_fused<T, CONT>(p, inst, smem, y, lane, tfree, bmin);
+    any = prepare_fused<T, CONT, COUNT>(p, inst, smem, y, lane, tfree, bmin);
 
   T *sC = (T *)(smem + y.C), *sA = (T *)(smem + y.A), *sB = (T *)(smem + y.B);
   T *sf = (T *)(smem + y.f), *seps = (T *)(smem + y.eps);
@@ -1316,7 +1564,8 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_solve_kernel(SolveArgs<T> args) 
   int nfeas = 0, nevals = 0;  // per lane
   if (any)
     search_candidates<T, FROM_TABLES, ONE_CHUNK, COUNT, GREEDY, CONT, QUEUE>(
-        p, tab, inst, smem, y, lane, N, blo, tfree, bestE, bestI, nfeas, nevals, !FROM_TABLES);
+        p, tab, inst, smem, y, lane, N, blo, tfree, uni(bmin) == 0 ? uni(sSL[0]) : inf_of<T>(),
+        gpu_energy_rate(p, smem, y, lane), bestE, bestI, nfeas, nevals, !FROM_TABLES);
 
   // local computing competes last
   const int idxLC = L * J * N;
@@ -1611,15 +1860,14 @@ __device__ inline void group_winner(const Problem<T> &p, int64_t inst, unsigned 
 // deadline order (a front of non-dominated (energy, release) states per
 // prefix; for each group j..i-1, one inner solve, search_candidates on the
 // group's users, per run of prefix j's states that share a winner), then
-// replays the chosen groups to write the policy.  Eight waves per SIMD: the
-// program's state and the inner search want more than 64 registers, and
-// fitting 64 spills a few values to scratch (outside the pass loops), but
-// the short passes of small groups wait on LDS and barriers, and the extra
-// resident waves hide that (measured: g10 22.5 ms at eight waves, 24.0 at
-// seven, 25.9 at six; p5 16.0, 16.3, 17.1; only g20, with groups of up to
-// 20 users, gains from fewer: 84.1, 82.9, 81.0).
+// replays the chosen groups to write the policy.  Seven waves per SIMD: the
+// program's state and the inner search want more than 64 registers; at seven
+// waves a few values still spill, outside the pass loops, but the short
+// searches of small groups wait on LDS, and resident waves hide that
+// (measured: 65,536 instances of 10 users 5.15 ms at eight and seven waves,
+// 5.39 at six and five; 4,239 of 6 users 389, 380, 369 and 369 us).
 template <typename T, bool ONE_CHUNK, bool COUNT, bool GREEDY, bool CONT>
-__global__ __launch_bounds__(WAVE, 8) void jdob_grouped_kernel(GroupedArgs<T> args) {
+__global__ __launch_bounds__(WAVE, 7) void jdob_grouped_kernel(GroupedArgs<T> args) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x;
   const Problem<T> p = own_problem(args.p);
@@ -1661,6 +1909,7 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_grouped_kernel(GroupedArgs<T> ar
   }
   __syncthreads();
 
+  const T rho = gpu_energy_rate(p, smem, y, lane);
   // The group's winner among its candidates and local computing: the flat
   // index (0x7fffffff if none is feasible), with the GPU free at tf0.
   // Counts into nf, ne when COUNT.
@@ -1668,7 +1917,8 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_grouped_kernel(GroupedArgs<T> ar
     T bestE = inf_of<T>();
     int bestI = 0x7fffffff;
     search_candidates<T, false, ONE_CHUNK, COUNT, GREEDY, CONT, false>(
-        p, tab, inst, smem, y, lane, g, bmin > 1 ? bmin : 1, tf0, bestE, bestI, nf, ne);
+        p, tab, inst, smem, y, lane, g, bmin > 1 ? bmin : 1, tf0,
+        bmin == 0 ? uni(sSL[0]) : inf_of<T>(), rho, bestE, bestI, nf, ne);
     wave_argmin(bestE, bestI);
     if (bmin == 0) {  // local computing of the whole group competes last
       if (COUNT) nf += (lane == 0) ? 1 : 0;

@@ -154,6 +154,20 @@ __device__ inline double lane_read(double v, int l) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// An associative, commutative op over each aligned run of 2^lg lanes; every
+// lane of the run gets the result (lg is wave-uniform).  Inside a row of 16
+// by DPP: quad permutes, then mirrors of the half row and the row (all lanes
+// of a half already agree).
+template <typename V, typename OP> __device__ inline V run_reduce(V v, int lg, OP op) {
+  if (lg >= 1) v = op(v, dpp_mov<0xB1, 0xf>(v, v));   // quad_perm [1,0,3,2]
+  if (lg >= 2) v = op(v, dpp_mov<0x4E, 0xf>(v, v));   // quad_perm [2,3,0,1]
+  if (lg >= 3) v = op(v, dpp_mov<0x141, 0xf>(v, v));  // row_half_mirror
+  if (lg >= 4) v = op(v, dpp_mov<0x140, 0xf>(v, v));  // row_mirror
+  if (lg >= 5) v = op(v, __shfl_xor(v, 16, WAVE));
+  if (lg >= 6) v = op(v, __shfl_xor(v, 32, WAVE));
+  return v;
+}
+
 // Lowest (energy, index) of the wave, lexicographically; every lane gets it.
 template <typename T>
 __device__ inline void wave_argmin(T &e, int &idx) {

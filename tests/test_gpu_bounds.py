@@ -1,0 +1,98 @@
+"""GPU parity where partition points and batches are dropped by energy bounds.
+
+The launches without work counters search only what a lower bound of the
+energy leaves, and the counters come from a walk of their own: both launches
+are compared with the oracle, at the sizes where the bounds' layout changes
+(one to three partition points, more than 64 of them, lanes per partition
+point from 1 to 64, batch sizes beyond one wave, GPU levels beyond one wave),
+with and without local computing as the energy to beat, on a busy GPU, and
+with users who are all alike.  The comparison is tests/parity.py's: the
+winner, its levels, energy and release time are the oracle's bit for bit,
+near-ties aside.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2504_14611_amd import jdob
+from paper_2504_14611_amd import workloads as W
+from tests.parity import compare
+from tests.test_gpu_grouped import compare_grouped
+
+pytestmark = pytest.mark.gpu
+
+# base (c2b: some users gain by offloading; p4a, p4b: all do; c4b: no local
+# computing; c3: local computing wins), instances, sizes
+SHAPES = [
+    ("c2b", 192, dict(N=12, L=1, K=8, J=8)),
+    ("c2b", 192, dict(N=12, L=2, K=8, J=8)),
+    ("c2b", 192, dict(N=12, L=3, K=8, J=8)),
+    ("p4a", 128, dict(N=10, L=16, J=33)),
+    ("p4b", 128, dict(N=10, L=17, J=64)),
+    ("c4b", 48, dict(N=64, L=33, K=16, J=48)),
+    ("c4b", 24, dict(N=130, L=63, K=8, J=70)),
+    ("p4b", 48, dict(N=65, L=64, J=12)),
+    ("c2b", 64, dict(N=20, L=65, K=5, J=65, cycles=("lu", 1e5, 1e7))),
+    ("c3", 256, dict(N=32, L=130, K=4, J=9, cycles=("lu", 1e5, 1e6))),
+    ("p4b", 12, dict(N=9, L=255, J=5)),
+    ("c2b", 96, dict(N=17, L=21, K=16, J=1)),
+]
+
+
+def both(prob, call):
+    """The policy without the work counters and with them, on the host."""
+    import torch
+    d = jdob.to_device(prob)
+    out = [jdob.to_host(call(d, counters=c, freq=True)) for c in (False, True)]
+    torch.cuda.synchronize()
+    return out
+
+
+def problem(base, n, mode, busy, dtype, seed, **kw):
+    p = W.generate(W.WORKLOADS[base].replace(name="bounds", stream=seed, num_instances=n, dtype=dtype, **kw))
+    p["mode"] = int(p["mode"]) | mode
+    if busy:
+        p["t_free"] = (0.4 * p["deadline"].min(axis=1)).astype(p["t_free"].dtype)
+    return p
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2, 8])
+@pytest.mark.parametrize("k", range(len(SHAPES)))
+def test_bounds_solve(k, mode):
+    base, n, kw = SHAPES[k]
+    dtype = "f64" if k % 5 == 4 and kw["N"] <= 64 else "f32"
+    prob = problem(base, n, mode, k % 2, dtype, 8000 + k, **kw)
+    label = f"bounds {base} {kw} mode={prob['mode']} {dtype}"
+    print(f"[gpu] {label}", flush=True)
+    ora = oracle.solve(prob, threads=16)
+    for gpu in both(prob, jdob.solve_batch):
+        compare(prob, gpu, ora, label=label)
+
+
+@pytest.mark.parametrize("mode", [0, 1, 4, 8])
+@pytest.mark.parametrize("base,n,kw", [("c2b", 48, dict(N=9, L=7, K=8, J=12)), ("g10", 48, dict(N=7, L=66, K=4, J=8)),
+                                       ("p5", 48, dict(N=8, L=3, J=65)), ("g20", 24, dict(N=13, L=32, K=16, J=7))])
+def test_bounds_grouped(base, n, kw, mode):
+    prob = problem(base, n, mode, mode == 4, "f32", 8100, **kw)
+    label = f"bounds grouped {base} {kw} mode={prob['mode']}"
+    print(f"[gpu] {label}", flush=True)
+    ora = oracle.solve_grouped(prob, threads=16)
+    for gpu in both(prob, jdob.solve_grouped):
+        compare_grouped(prob, gpu, ora, label)
+
+
+def test_bounds_joint_takes_upload_times_from_its_tables():
+    """The joint call reads the upload times of its tables, not the rates:
+    with the times of another problem it answers that problem."""
+    import torch
+    p = problem("c2b", 96, 0, False, "f32", 8200, N=20, L=22, K=16, J=16)
+    q = dict(p)
+    q["bits"] = (p["bits"] * np.float32(0.25)).astype(np.float32)
+    dp, dq = jdob.to_device(p), jdob.to_device(q)
+    want = jdob.to_host(jdob.solve_batch(dq, counters=False))
+    got = jdob.to_host(jdob.eval_joint(dp, jdob.eval_user_tables(dq), counters=False))
+    torch.cuda.synchronize()
+    for k in want:
+        if want[k] is not None:
+            assert np.array_equal(want[k], got[k]), k
