@@ -472,11 +472,6 @@ __device__ void prepare_instance(const Problem<T> &p, const Tables<T> &tab, int6
   bmin_out = bmin;
 }
 
-// Wave-wide minimum and maximum (every lane gets the value).
-template <typename T> __device__ inline T wave_min(T v) {
-  v = wave_iscan(v, inf_of<T>(), [](T a, T b) { return b < a ? b : a; });
-  return lane_read(v, WAVE - 1);
-}
 __device__ inline int wave_min_int(int v) {
   v = wave_iscan(v, 0x7fffffff, [](int a, int b) { return b < a ? b : a; });
   return lane_read(v, WAVE - 1);
@@ -484,54 +479,6 @@ __device__ inline int wave_min_int(int v) {
 __device__ inline int wave_sum_int(int v) {
   v = wave_iscan(v, 0, [](int a, int b) { return a + b; });
   return lane_read(v, WAVE - 1);
-}
-
-// Energy bounds.  A candidate's ranking energy is a sum of non-negative terms,
-// so a sum with every term replaced by a lower bound of it cannot exceed it by
-// more than rounding: at most about 2 N roundings of 2^-24 (binary32, N <=
-// 1024: 1.2e-4, and the hardware reciprocals' ulps).  A bound that exceeds the
-// energy of some candidate (inc) by 2^-12 of itself therefore belongs to
-// candidates that neither win nor tie: they need not be evaluated.
-template <typename T> __device__ inline bool beaten(T lb, T inc) {
-  return lb * T(1.0 - 0x1p-12) > inc;
-}
-
-// Hardware reciprocal, for bounds.
-__device__ inline float rough_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ inline double rough_rcp(double x) { return __builtin_amdgcn_rcp(x); }
-
-// A little less than 1 / x (x > 0; the hardware's reciprocal of a denormal is
-// infinite).
-__device__ inline float rcp_below(float x) {
-  const float q = rough_rcp(x) * (1.0f - 0x1p-20f);
-  return q < 0x1p126f ? q : 0x1p126f;
-}
-__device__ inline double rcp_below(double x) {
-  const double q = rough_rcp(x) * (1.0 - 0x1p-20);
-  return q < 0x1p1022 ? q : 0x1p1022;
-}
-
-// CPU energy kC * f^2 (kC = kappa * C[s]) of a user with budget x or less, from
-// below: the lowest frequency finishing Cs cycles by then, at least f0 (also
-// where x <= 0 or Cs = 0 makes the quotient negative or NaN).
-template <typename T> __device__ inline T least_cpu(T Cs, T kC, T x, T f0) {
-  const T q = Cs * rough_rcp(x);
-  const T f = q > f0 ? q : f0;
-  return kC * (f * f);
-}
-
-// Lowest GPU energy per second of batch latency at the top level, over the
-// GPU levels searched: P_j * Phi_j >= rho * (A[s] + B[s]*b).
-template <typename T>
-__device__ inline T gpu_energy_rate(const Problem<T> &p, const unsigned char *smem, const Layout &y,
-                                    int lane) {
-  const T *sr = (const T *)(smem + y.r), *sP = (const T *)(smem + y.P);
-  T v = inf_of<T>();
-  for (int j = p.j_low + lane; j < p.J; j += WAVE) {
-    const T e = sP[j] * sr[j];
-    v = e < v ? e : v;
-  }
-  return wave_min(v);
 }
 
 // Base-2 logarithm of the lanes that one of n items can have when the wave
@@ -556,7 +503,7 @@ __device__ inline bool drop_beaten(const Problem<T> &p, unsigned char *smem, con
   const T *sB = (const T *)(smem + y.B), *seps = (const T *)(smem + y.eps);
   const T *seL = (const T *)(smem + y.eL);
   int8_t *sflag = (int8_t *)(smem + y.sflag);
-  const T rho = gpu_energy_rate(p, smem, y, lane);
+  const T rho = gpu_energy_rate((const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, p.J, lane);
   T lc = T(0);
   for (int m = lane; m < N; m += WAVE) lc = lc + seL[m];
   lc = lane_read(wave_iscan(lc, T(0), [](T a, T b) { return a + b; }), WAVE - 1);
@@ -1565,7 +1512,7 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_solve_kernel(SolveArgs<T> args) 
   if (any)
     search_candidates<T, FROM_TABLES, ONE_CHUNK, COUNT, GREEDY, CONT, QUEUE>(
         p, tab, inst, smem, y, lane, N, blo, tfree, uni(bmin) == 0 ? uni(sSL[0]) : inf_of<T>(),
-        gpu_energy_rate(p, smem, y, lane), bestE, bestI, nfeas, nevals, !FROM_TABLES);
+        gpu_energy_rate(sr, sP, p.j_low, J, lane), bestE, bestI, nfeas, nevals, !FROM_TABLES);
 
   // local computing competes last
   const int idxLC = L * J * N;
@@ -1909,7 +1856,7 @@ __global__ __launch_bounds__(WAVE, 7) void jdob_grouped_kernel(GroupedArgs<T> ar
   }
   __syncthreads();
 
-  const T rho = gpu_energy_rate(p, smem, y, lane);
+  const T rho = gpu_energy_rate((const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, J, lane);
   // The group's winner among its candidates and local computing: the flat
   // index (0x7fffffff if none is feasible), with the GPU free at tf0.
   // Counts into nf, ne when COUNT.

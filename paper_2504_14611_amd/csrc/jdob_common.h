@@ -201,6 +201,11 @@ __device__ inline int64_t wave_sum_i64(int64_t v) {
   return v;
 }
 
+// Wave-wide minimum and maximum (every lane gets the value).
+template <typename T> __device__ inline T wave_min(T v) {
+  v = wave_iscan(v, inf_of<T>(), [](T a, T b) { return b < a ? b : a; });
+  return lane_read(v, WAVE - 1);
+}
 template <typename T>
 __device__ inline T wave_max(T v) {
   v = wave_iscan(v, -inf_of<T>(), [](T a, T b) { return b > a ? b : a; });
@@ -213,6 +218,52 @@ template <typename T, bool IS_MIN>
 __device__ inline T wave_scan(T v, int) {
   if (IS_MIN) return wave_iscan(v, inf_of<T>(), [](T a, T b) { return b < a ? b : a; });
   return wave_iscan(v, T(0), [](T a, T b) { return a + b; });
+}
+
+// Energy bounds.  A candidate's ranking energy is a sum of non-negative terms,
+// so a sum with every term replaced by a lower bound of it cannot exceed it by
+// more than rounding: at most about 2 N roundings of 2^-24 (binary32, N <=
+// 1024: 1.2e-4, and the hardware reciprocals' ulps).  A bound that exceeds the
+// energy of some candidate (inc) by 2^-12 of itself therefore belongs to
+// candidates that neither win nor tie: they need not be evaluated.
+template <typename T> __device__ inline bool beaten(T lb, T inc) {
+  return lb * T(1.0 - 0x1p-12) > inc;
+}
+
+// Hardware reciprocal, for bounds.
+__device__ inline float rough_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ inline double rough_rcp(double x) { return __builtin_amdgcn_rcp(x); }
+
+// A little less than 1 / x (x > 0; the hardware's reciprocal of a denormal is
+// infinite).
+__device__ inline float rcp_below(float x) {
+  const float q = rough_rcp(x) * (1.0f - 0x1p-20f);
+  return q < 0x1p126f ? q : 0x1p126f;
+}
+__device__ inline double rcp_below(double x) {
+  const double q = rough_rcp(x) * (1.0 - 0x1p-20);
+  return q < 0x1p1022 ? q : 0x1p1022;
+}
+
+// CPU energy kC * f^2 (kC = kappa * C[s]) of a user with budget x or less, from
+// below: the lowest frequency finishing Cs cycles by then, at least f0 (also
+// where x <= 0 or Cs = 0 makes the quotient negative or NaN).
+template <typename T> __device__ inline T least_cpu(T Cs, T kC, T x, T f0) {
+  const T q = Cs * rough_rcp(x);
+  const T f = q > f0 ? q : f0;
+  return kC * (f * f);
+}
+
+// Lowest GPU energy per second of batch latency at the top level, over the
+// GPU levels searched: P_j * Phi_j >= rho * (A[s] + B[s]*b).
+template <typename T>
+__device__ inline T gpu_energy_rate(const T *sr, const T *sP, int j_low, int J, int lane) {
+  T v = inf_of<T>();
+  for (int j = j_low + lane; j < J; j += WAVE) {
+    const T e = sP[j] * sr[j];
+    v = e < v ? e : v;
+  }
+  return wave_min(v);
 }
 
 // A copy of a uniform value in scalar registers of its own.  Kernel arguments

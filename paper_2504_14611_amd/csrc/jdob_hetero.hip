@@ -9,10 +9,13 @@
 // lane per user wherever per-user work is done):
 //   1. coalesced loads; the sums C, A, B in the pinned order; each user's
 //      local-only level and energy (constraint (8), Eq. (20));
-//   2. per partition point s: each user's gamma, its rank by comparison
-//      counting (ties: lower index), its level row (Eqs. (1), (2)) and the
-//      smallest slack at which it meets (7) at its top frequency; then min-,
-//      max- and sum-scans along pi_s give the batch records;
+//   2. several partition points at a time: each user's gamma, its rank by
+//      comparison counting (ties: lower index) and the smallest slack at which
+//      it meets (7) at its top frequency; min-, max- and sum-scans along pi_s
+//      give a lower bound of the partition point's energy.  The partition
+//      points are searched best bound first, until the bound exceeds the best
+//      energy found (hbounds); in those, the same scans give the batch records
+//      and the batches worth a pass, and the level rows are built;
 //   3. passes over (GPU level j x batch b) or, in the greedy mode, one batch
 //      per level found by binary search; each lane walks its offloaders:
 //      the level is the number of the user's levels too slow for the budget
@@ -31,6 +34,8 @@
 // of the dynamic program as an instance of its own.
 
 #include "jdob_common.h"
+
+#include <type_traits>
 
 namespace jdob_dev {
 namespace {
@@ -86,14 +91,17 @@ template <typename T> struct UserOut {
 // latency, its work zeta*C[s], its frequency range (continuous mode).
 template <typename T> struct alignas(4 * sizeof(T)) HUser { T up, z, fmin, fmax; };
 
+// A user in the gamma order of a partition point: its upload latency, need
+// (slack_needed), work zeta*C[s], and its index m.
+template <typename T> struct alignas(4 * sizeof(T)) HPos { T up, need, z, m; };
+
 // Byte offsets of the per-instance LDS arrays.
 struct HLayout {
   int cyc, al, be, bits, C, A, B, r, P;           // layers and GPU levels
   int rate, dl, zet, kap, ptx, lf, kL, eL, fL;    // per user (index m)
-  int gam, key, need;                             // per user, current s
-  int pi, usr, kc, lv, bt, term;                  // per position in pi_s
+  int gam, need, pi, usr, kc, lv, bt, term;       // per position in pi_s
   int drank, dord, fE, fT, from, fn, ends, eks;  // the grouping program
-  int pre;                                        // per (s, user) table of the grouping, -1: none
+  int tab;                                        // the grouping's orders, -1: none
   int K4, total;
 };
 
@@ -123,14 +131,15 @@ __host__ __device__ inline HLayout make_hlayout(int N, int L, int K, int J, int 
   y.kL = take(N * 4);
   y.eL = take(N * szT);
   y.fL = take(N * szT);
-  y.gam = take(N * szT);
-  y.key = take32(((N + 1) & ~1) * 8);          // rank keys (binary32), even count
+  y.gam = take(N * szT);                       // bound of the first b users' CPU energy
   y.need = take(N * szT);
   y.pi = take(N * 4);
   y.usr = take32((N + 1) * 4 * szT);           // HUser by position (+1: read-ahead)
   y.kc = take(N * szT);                        // kappa * C[s] by position
   y.lv = take32(N * y.K4 * 2 * szT);           // Level rows by position, K4 apart
-  y.bt = take32((N + 2 + WAVE) * 4 * szT);     // Batch records, b = 1..N (+ sentinels)
+  // Batch records, b = 1..N (+ sentinels); before they are stored, the keys of
+  // a gamma order and then its records (64 of each)
+  y.bt = take32((N + 2 + WAVE) * 4 * szT);
   y.term = take(N * szT);
   y.drank = y.dord = y.fE = y.fT = y.from = y.fn = y.ends = y.eks = 0;
   if (grouped) {
@@ -144,16 +153,16 @@ __host__ __device__ inline HLayout make_hlayout(int N, int L, int K, int J, int 
     y.ends = take((N + 1) * 4);      // ends of the chosen groups, in order
     y.eks = take((N + 1) * 4);       // the chosen state at each end
   }
-  // The grouping meets every partition point once per group: each user's
-  // upload latency, top-level latency and need at s (none depends on the
-  // group) are kept per (s, user) where the table costs no occupancy (the
-  // workgroups that fit a CU's LDS, at most 32 of one wave each) and stays
+  // The grouping meets every partition point once per group: the gamma order
+  // of all users, which holds every group's, with each one's HPos record, is
+  // kept per partition point where the table costs no occupancy (the
+  // workgroups that fit a CU's LDS, at most 24 of one wave each) and stays
   // within the limit of one workgroup.
-  y.pre = -1;
-  const int pre_bytes = L * N * 3 * szT;
-  auto per_cu = [](int bytes) { const int w = LDS_PER_CU / (bytes > 0 ? bytes : 1); return w < 32 ? w : 32; };
-  if (grouped && align8(o) + pre_bytes <= LDS_LIMIT && per_cu(align8(o) + pre_bytes) == per_cu(o))
-    y.pre = take(pre_bytes);
+  y.tab = -1;
+  const int base = (o + 31) & ~31, tab_bytes = L * N * 4 * szT;
+  auto per_cu = [](int bytes) { const int w = LDS_PER_CU / (bytes > 0 ? bytes : 1); return w < 24 ? w : 24; };
+  if (grouped && base + tab_bytes <= LDS_LIMIT && per_cu(base + tab_bytes) == per_cu(o))
+    y.tab = take32(tab_bytes);
   y.total = o;
   return y;
 }
@@ -267,117 +276,238 @@ __device__ void hprepare(const HProblem<T> &p, int64_t inst, unsigned char *smem
   __syncthreads();
 }
 
-// Each user's top-level latency, upload latency and need (Eqs. (1), (3),
-// reading 31) at a run of partition points, computed together: lane
-// r*W + m holds user m's at partition point s0 + r, W = 16, 32 or 64 lanes
-// per point (the solve meets its partition points in order).
-template <typename T> struct HRowCache {
-  int s0 = -1;
-  T tk = T(0), up = T(0), nd = T(0);
-};
+// Rank of the lane's user in the gamma order of its partition point: users
+// with a lower gamma come first, ties by lower index.  An aligned run of 2^lg
+// lanes holds one partition point's users (lane m of the run user m, N of
+// them); `mem` marks those ranked among each other.  In binary32 the 64-bit
+// key (gamma bits, index) orders them the same way (gamma >= +0: a sum of a
+// non-negative quotient and +0 or more, and non-negative IEEE values order
+// like their bit patterns); the others, and the pad to an even count, get the
+// largest key.  Two keys per read, one compare each.
+__device__ inline int gamma_rank(float g, bool mem, int N, int lg, uint64_t *skey, int lane) {
+  const int m = lane & ((1 << lg) - 1);
+  const uint64_t me = mem ? ((uint64_t)__float_as_uint(g) << 32) | (uint32_t)m : ~(uint64_t)0;
+  skey[lane] = me;
+  __syncthreads();
+  const uint64_t *k = skey + (lane - m);
+  int pos = 0;
+  for (int q = 0; q < N; q += 2) {  // (the run holds N + 1 lanes or N is even)
+    const ulonglong2 kk = *(const ulonglong2 *)(k + q);
+    pos += (kk.x < me ? 1 : 0) + (kk.y < me ? 1 : 0);
+  }
+  return pos;
+}
+__device__ inline int gamma_rank(double g, bool mem, int N, int lg, uint64_t *skey, int lane) {
+  const int m = lane & ((1 << lg) - 1);
+  double *sg = (double *)skey;
+  sg[lane] = mem ? g : inf_of<double>();
+  __syncthreads();
+  const double *k = sg + (lane - m);
+  int pos = 0;
+  for (int q = 0; q < N; ++q) pos += (k[q] < g || (k[q] == g && q < m)) ? 1 : 0;
+  return pos;
+}
+
+// The record and gamma (Eq. (17)) of user m at partition point s.
+template <typename T>
+__device__ inline HPos<T> user_at(const unsigned char *smem, const HLayout &y, int K, int s, int m,
+                                  T *gamma) {
+  HPos<T> u;
+  u.z = ((const T *)(smem + y.zet))[m] * ((const T *)(smem + y.C))[s];      // cycles of layers 1..s
+  const T tK1 = u.z / ((const T *)(smem + y.lf))[m * K + K - 1];            // Eq. (1), top level
+  u.up = ((const T *)(smem + y.bits))[s] / ((const T *)(smem + y.rate))[m];  // Eq. (3)
+  u.need = slack_needed(tK1, u.up);
+  u.m = T(m);
+  *gamma = u.up + tK1;
+  return u;
+}
+
+// The gamma order pi_s of the users in mask, position by position: index,
+// record, kappa * C[s] and need.
+template <typename T>
+__device__ inline void horder(const HProblem<T> &p, unsigned char *smem, const HLayout &y, int lane,
+                              int s, uint64_t mask) {
+  const int N = p.N, K = p.K;
+  const T *slf = (const T *)(smem + y.lf);
+  HPos<T> u;
+  bool mem;
+  int pos, m;
+  if (y.tab >= 0) {  // the members of the full order, in that order
+    u = ((const HPos<T> *)(smem + y.tab))[s * N + (lane < N ? lane : 0)];
+    m = (int)u.m;
+    mem = lane < N && ((mask >> m) & 1);
+    const uint64_t mm = __builtin_amdgcn_ballot_w64(mem);
+    pos = __builtin_amdgcn_mbcnt_hi((unsigned)(mm >> 32),
+                                    __builtin_amdgcn_mbcnt_lo((unsigned)mm, 0u));
+  } else {
+    m = lane;
+    mem = (mask >> lane) & 1;
+    T g;
+    u = user_at(smem, y, K, s, lane < N ? lane : 0, &g);
+    pos = gamma_rank(g, mem, N, 6, (uint64_t *)(smem + y.bt), lane);
+  }
+  if (mem) {
+    ((int *)(smem + y.pi))[pos] = m;
+    HUser<T> v;
+    v.up = u.up;
+    v.z = u.z;
+    v.fmin = slf[m * K];
+    v.fmax = slf[m * K + K - 1];
+    ((HUser<T> *)(smem + y.usr))[pos] = v;
+    ((T *)(smem + y.kc))[pos] = ((const T *)(smem + y.kap))[m] * ((const T *)(smem + y.C))[s];
+    ((T *)(smem + y.need))[pos] = u.need;
+  }
+  __syncthreads();
+}
+
+// Inclusive scan over each aligned run of 2^lg >= 16 lanes (the steps of
+// wave_iscan that stay inside it).
+template <typename V, typename OP> __device__ inline V run_iscan(V v, V id, int lg, OP op) {
+  v = op(v, dpp_mov<0x111, 0xf>(id, v));  // row_shr:1
+  v = op(v, dpp_mov<0x112, 0xf>(id, v));  // row_shr:2
+  v = op(v, dpp_mov<0x114, 0xf>(id, v));  // row_shr:4
+  v = op(v, dpp_mov<0x118, 0xf>(id, v));  // row_shr:8
+  if (lg >= 5) v = op(v, dpp_mov<0x142, 0xa>(id, v));  // row_bcast:15 into rows 1, 3
+  if (lg >= 6) v = op(v, dpp_mov<0x143, 0xc>(id, v));  // row_bcast:31 into rows 2, 3
+  return v;
+}
+
+// Suffix sums over lanes 0..n-1 (v is zero past n): steps of 1, 2, 4, ...
+// lanes, by DPP inside a row of 16.
+template <typename T> __device__ inline T suffix_sum(T v, int n, int lane) {
+  if (n <= 16) {
+    v = v + dpp_mov<0x101, 0xf>(T(0), v);  // row_shl:1
+    if (n > 2) v = v + dpp_mov<0x102, 0xf>(T(0), v);
+    if (n > 4) v = v + dpp_mov<0x104, 0xf>(T(0), v);
+    if (n > 8) v = v + dpp_mov<0x108, 0xf>(T(0), v);
+    return v;
+  }
+  for (int d = 1; d < n; d <<= 1) {
+    const T o = __shfl_down(v, d, WAVE);
+    v = v + ((lane + d < n) ? o : T(0));
+  }
+  return v;
+}
+
+// The number of GPU levels at which a batch with deadline lo, need nd and
+// batch latency ab at the top level is feasible: the highest ones, down to one
+// found by binary search.
+template <typename T>
+__device__ inline int feasible_levels(const HProblem<T> &p, const T *sr, T lo, T nd, T ab,
+                                      T tfree) {
+  const int Jn = p.J - p.j_low;
+  int low = 0;  // levels that miss a deadline
+  for (int step = 1 << (31 - __clz(Jn)); step > 0; step >>= 1) {
+    const int c = low + step;
+    const T H = lo - ab * sr[c <= Jn ? p.j_low + c - 1 : p.J - 1];
+    low = (c <= Jn && !(H >= tfree && H >= nd)) ? c : low;
+  }
+  return Jn - low;
+}
+
+// Lower bounds of the partition points' energies for the users in mask, with
+// the GPU free at tfree, into slb[s] (+inf: no feasible candidate).  Lanes
+// take (partition point, position in its gamma order), 64, 32 or 16 lanes a
+// point.  A batch size b is bounded by the least GPU energy, the upload
+// energy of the first b users, the local energy of the others, and the CPU
+// energy of each offloader at the lowest frequency at which it could close a
+// batch of its own, which no larger batch lets it go below; feasibility
+// falls with b and rises with j, so the test is that of the top GPU level.
+// (16 users, 22 layers: 6.5 of 21.5 partition points with feasible candidates
+// are then searched, best bound first; 17 of the batches of 72 passes.)
+// Counts the feasible candidates into nfeas, nevals when COUNT.
+template <typename T, bool COUNT>
+__device__ void hbounds(const HProblem<T> &p, unsigned char *smem, const HLayout &y, int lane,
+                        uint64_t mask, T tfree, T rho, T *slb, int &nfeas, int64_t &nevals) {
+  const int N = p.N, K = p.K, J = p.J;
+  const T *sC = (const T *)(smem + y.C), *sA = (const T *)(smem + y.A);
+  const T *sB = (const T *)(smem + y.B), *sr = (const T *)(smem + y.r);
+  const int lg = N <= 16 ? 4 : (N <= 32 ? 5 : 6), W = 1 << lg;
+  const int r = lane >> lg, q = lane & (W - 1);
+  const T rtop = sr[J - 1];
+  for (int s0 = 0; s0 < p.s_end; s0 += WAVE >> lg) {
+    const bool in = q < N && s0 + r < p.s_end;
+    const int s = in ? s0 + r : 0;
+    HPos<T> u;
+    if (y.tab >= 0) {
+      u = ((const HPos<T> *)(smem + y.tab))[s * N + (in ? q : 0)];
+    } else {  // this run's orders, in the room of the batch records
+      HPos<T> *scratch = (HPos<T> *)(smem + y.bt);
+      T g;
+      const HPos<T> v = user_at(smem, y, K, s, in ? q : 0, &g);
+      const int pos = gamma_rank(g, in, N, lg, (uint64_t *)(smem + y.bt), lane);
+      if (in) scratch[(lane - q) + pos] = v;
+      __syncthreads();
+      u = scratch[in ? lane : 0];
+    }
+    const int m = in ? (int)u.m : 0;
+    const bool mem = in && ((mask >> m) & 1);
+    const uint64_t mm = __builtin_amdgcn_ballot_w64(mem) >> (lane - q);
+    const int b = __popcll(mm & ((uint64_t(2) << q) - 1));  // batch closed by this user
+    const T lo = run_iscan(mem ? ((const T *)(smem + y.dl))[m] : inf_of<T>(), inf_of<T>(), lg,
+                           [](T a, T b) { return b < a ? b : a; });
+    const T nd = run_iscan(mem ? u.need : -inf_of<T>(), -inf_of<T>(), lg,
+                           [](T a, T b) { return b > a ? b : a; });
+    const T ab = sA[s] + sB[s] * T(b), H = lo - ab * rtop;
+    const T cpu = least_cpu(u.z, ((const T *)(smem + y.kap))[m] * sC[s], H - u.up,
+                            ((const T *)(smem + y.lf))[m * K]);
+    const T off = run_iscan(mem ? fma_(((const T *)(smem + y.ptx))[m], u.up, cpu) : T(0), T(0), lg,
+                            [](T a, T b) { return a + b; });
+    // the others' local energy: suffix sums less the user's own
+    const T eL = mem ? ((const T *)(smem + y.eL))[m] : T(0);
+    T sl = eL;
+    if (lg == 4) {
+      sl = sl + dpp_mov<0x101, 0xf>(T(0), sl);  // row_shl:1
+      sl = sl + dpp_mov<0x102, 0xf>(T(0), sl);
+      sl = sl + dpp_mov<0x104, 0xf>(T(0), sl);
+      sl = sl + dpp_mov<0x108, 0xf>(T(0), sl);
+      sl = dpp_mov<0x101, 0xf>(T(0), sl);
+    } else {
+      for (int d = 1; d < W; d <<= 1) {
+        const T o = __shfl_down(sl, d, W);
+        sl = sl + (q + d < W ? o : T(0));
+      }
+      const T o = __shfl_down(sl, 1, W);
+      sl = q + 1 < W ? o : T(0);
+    }
+    // (sl is infinite where a user left local misses its deadline, (8))
+    const bool ok = mem & (H >= tfree) & (H >= nd) & (sl < inf_of<T>());
+    if constexpr (COUNT) {
+      const int c = feasible_levels(p, sr, lo, nd, ab, tfree);
+      nfeas += ok ? c : 0;
+      nevals += ok ? c * b : 0;
+    }
+    const T lb = run_reduce(ok ? fma_(rho, ab, off + sl) : inf_of<T>(), lg,
+                            [](T a, T b) { return b < a ? b : a; });
+    if (q == 0 && s0 + r < p.s_end) slb[s0 + r] = lb;
+    __syncthreads();
+  }
+}
 
 // Partition point s for the users in mask (n of them): the gamma order
-// pi_s of those users, each one's record and, if the partition point has a
-// feasible candidate (the test at the top GPU level and the smallest
-// admissible batch, from the scans before any record is stored;
-// feasibility only falls with b and rises with j) or `records` asks for
-// them, the batch records b = 1..n, and then the level rows.  Returns bmin
-// and sets *any (both wave-uniform).
-template <typename T, bool CONT>
+// pi_s of those users and each one's record; then, if a batch is worth a
+// pass, the batch records b = 1..n and the level rows.  A batch is worth a
+// pass if it is feasible at the top GPU level and its bound (see hbounds) is
+// not beaten by inc.  The tests use the scans, before anything is stored.
+// Returns bmin and sets *todo, bit b - 1 for batch size b (both
+// wave-uniform); counts the feasible candidates as hbounds does when COUNT.
+template <typename T, bool CONT, bool COUNT>
 __device__ int hrow(const HProblem<T> &p, int64_t inst, unsigned char *smem, const HLayout &y,
-                    int lane, int s, T tfree, uint64_t mask, int n, bool *any,
-                    bool records = false, HRowCache<T> *hc = nullptr) {
-  const int L = p.L, K = p.K, K4 = y.K4;
+                    int lane, int s, T tfree, uint64_t mask, int n, T inc, T rho, uint64_t *todo,
+                    int &nfeas, int64_t &nevals) {
+  const int K = p.K, K4 = y.K4;
   const T *sC = (const T *)(smem + y.C), *sA = (const T *)(smem + y.A);
-  const T *sB = (const T *)(smem + y.B);
-  const T *srate = (const T *)(smem + y.rate), *sdl = (const T *)(smem + y.dl);
-  const T *szet = (const T *)(smem + y.zet), *skap = (const T *)(smem + y.kap);
-  const T *sptx = (const T *)(smem + y.ptx), *slf = (const T *)(smem + y.lf);
-  const int *skL = (const int *)(smem + y.kL);
-  const T *seL = (const T *)(smem + y.eL);
-  T *sgam = (T *)(smem + y.gam), *sneed = (T *)(smem + y.need);
-  uint64_t *skey = (uint64_t *)(smem + y.key);
-  int *spi = (int *)(smem + y.pi);
-  HUser<T> *susr = (HUser<T> *)(smem + y.usr);
-  T *skc = (T *)(smem + y.kc);
+  const T *sB = (const T *)(smem + y.B), *sdl = (const T *)(smem + y.dl);
+  const T *skap = (const T *)(smem + y.kap), *sptx = (const T *)(smem + y.ptx);
+  const T *slf = (const T *)(smem + y.lf), *seL = (const T *)(smem + y.eL);
+  const int *skL = (const int *)(smem + y.kL), *spi = (const int *)(smem + y.pi);
+  T *scl = (T *)(smem + y.gam);
+  const HUser<T> *susr = (const HUser<T> *)(smem + y.usr);
+  const T *skc = (const T *)(smem + y.kc), *sneed = (const T *)(smem + y.need);
   Level<T> *slv = (Level<T> *)(smem + y.lv);
   Batch<T> *sbt = (Batch<T> *)(smem + y.bt);
-
-  const bool mem = (mask >> lane) & 1;  // lane = user m of the instance
   const T Cs = sC[s];
-  T up = T(0), W = T(0), tK1 = T(0);
-  const T *pre = y.pre >= 0 ? (const T *)(smem + y.pre) + (s * p.N + lane) * 3 : nullptr;
-  T ndc = T(0);
-  if (hc && !pre) {
-    const int lps = p.N <= 16 ? 16 : (p.N <= 32 ? 32 : WAVE), R = WAVE / lps;
-    if (hc->s0 < 0 || s < hc->s0 || s >= hc->s0 + R) {
-      hc->s0 = s;
-      const int r = lane / lps, mu = lane - r * lps, sb = s + r;
-      T tk = T(0), u = T(0), nd = T(0);
-      if (mu < p.N && sb < p.s_end) {
-        const T Wb = szet[mu] * sC[sb];
-        tk = Wb / slf[mu * K + K - 1];
-        u = ((const T *)(smem + y.bits))[sb] / srate[mu];
-        nd = slack_needed(tk, u);
-      }
-      hc->tk = tk;
-      hc->up = u;
-      hc->nd = nd;
-    }
-    const int src = (s - hc->s0) * lps + (lane < lps ? lane : 0);
-    tK1 = __shfl(hc->tk, src, WAVE);
-    up = __shfl(hc->up, src, WAVE);
-    ndc = __shfl(hc->nd, src, WAVE);
-  }
-  if (mem) {
-    W = szet[lane] * Cs;                               // cycles of layers 1..s
-    if (pre) {                                         // the grouping's table
-      up = pre[0];
-      tK1 = pre[1];
-    } else if (!hc) {
-      tK1 = W / slf[lane * K + K - 1];                 // Eq. (1) at the top level
-      up = ((const T *)(smem + y.bits))[s] / srate[lane];  // Eq. (3)
-    }
-    sgam[lane] = up + tK1;                             // Eq. (17)
-  }
-  // Rank of each member among the members: those with a lower gamma, or an
-  // equal one and a lower index.  In binary32 the 64-bit key (gamma bits,
-  // index) orders the members the same way (gamma >= +0: a sum of a
-  // non-negative quotient and +0 or more, and non-negative IEEE values order
-  // like their bit patterns); the other users, and the pad to an even
-  // count, get the largest key.  Two keys per read, one compare each.
-  const int N2 = (p.N + 1) & ~1;
-  if (sizeof(T) == 4 && lane < N2)
-    skey[lane] = mem ? ((uint64_t)__float_as_uint((float)(up + tK1)) << 32) | (uint32_t)lane
-                     : ~(uint64_t)0;
-  __syncthreads();
-  if (mem) {
-    int pos = 0;
-    if (sizeof(T) == 4) {
-      const uint64_t me = skey[lane];
-      for (int q = 0; q < N2; q += 2) {
-        const ulonglong2 kk = *(const ulonglong2 *)(skey + q);
-        pos += (kk.x < me ? 1 : 0) + (kk.y < me ? 1 : 0);
-      }
-    } else {
-      const T g = sgam[lane];
-      for (uint64_t mm = mask; mm; mm &= mm - 1) {   // the other members
-        const int q = __builtin_ctzll(mm);
-        const T gq = sgam[q];
-        pos += (gq < g || (gq == g && q < lane)) ? 1 : 0;
-      }
-    }
-    spi[pos] = lane;
-    HUser<T> u;
-    u.up = up;
-    u.z = W;
-    u.fmin = slf[lane * K];
-    u.fmax = slf[lane * K + K - 1];
-    susr[pos] = u;
-    skc[pos] = skap[lane] * Cs;
-    sneed[pos] = pre ? pre[2] : (hc ? ndc : slack_needed(tK1, up));
-  }
-  __syncthreads();
+  horder<T>(p, smem, y, lane, s, mask);
   // along pi_s (lane = position): lo = prefix min of deadlines (Eq. (10)),
   // the prefix max of need, bmin, the upload energy EU and the local
   // energies SL of the others (ranking only); scans over n positions
@@ -385,35 +515,51 @@ __device__ int hrow(const HProblem<T> &p, int64_t inst, unsigned char *smem, con
   const int m = in ? spi[lane] : 0;
   T lo = in ? sdl[m] : inf_of<T>(), nd = in ? sneed[lane] : -inf_of<T>();
   T sl = in ? seL[m] : T(0);
-  // the minimum and the maximum are exact in any order: DPP scans
-  lo = wave_iscan(lo, inf_of<T>(), [](T a, T b) { return b < a ? b : a; });
-  nd = wave_iscan(nd, -inf_of<T>(), [](T a, T b) { return b > a ? b : a; });
+  // (up to 16 users, one row of lanes holds them all)
+  const int lg = n <= 16 ? 4 : 6;
+  lo = run_iscan(lo, inf_of<T>(), lg, [](T a, T b) { return b < a ? b : a; });
+  nd = run_iscan(nd, -inf_of<T>(), lg, [](T a, T b) { return b > a ? b : a; });
   const uint64_t nolocal = __builtin_amdgcn_ballot_w64(in && skL[m] < 0);
   const int bmin = nolocal ? 64 - __clzll((long long)nolocal) : 0;
-  // the test, with the operations of batch record blo: lo and the largest
-  // need at position blo - 1, A[s] + B[s]*blo
   const int blo = bmin > 1 ? bmin : 1;
-  bool ok = false;
-  if (blo <= n) {
-    const T ab = sA[s] + sB[s] * T(blo);
-    const T H = lane_read(lo, blo - 1) - ab * ((const T *)(smem + y.r))[p.J - 1];
-    ok = (H >= tfree) && (H >= lane_read(nd, blo - 1));
+  const T *sr = (const T *)(smem + y.r);
+  const T ab = sA[s] + sB[s] * T(lane + 1);  // batch size lane + 1
+  const T Htop = lo - ab * sr[p.J - 1];
+  // the tests, with the operations of the passes
+  uint64_t ok = __builtin_amdgcn_ballot_w64(in && lane + 1 >= blo && Htop >= tfree && Htop >= nd);
+  *todo = 0;
+  if (!ok) return bmin;
+  if constexpr (COUNT) {
+    const int c = feasible_levels(p, sr, lo, nd, ab, tfree);
+    if ((ok >> lane) & 1) {
+      nfeas += c;
+      nevals += c * (lane + 1);
+    }
   }
-  *any = ok;
-  if (!ok && !records) return bmin;
-  for (int d = 1; d < n; d <<= 1) {
-    const T nsl = __shfl_down(sl, d, WAVE);
-    sl = sl + ((lane + d < n) ? nsl : T(0));
+  const HUser<T> us = susr[in ? lane : 0];
+  sl = suffix_sum(sl, n, lane);
+  auto add = [](T a, T b) { return a + b; };
+  const T eu = run_iscan(in ? sptx[m] * us.up : T(0), T(0), lg, add);
+  T slnext;  // over positions > lane
+  if (n <= 16) {
+    slnext = dpp_mov<0x101, 0xf>(T(0), sl);
+  } else {
+    slnext = __shfl_down(sl, 1, WAVE);
+    slnext = lane + 1 < n ? slnext : T(0);
   }
-  const T eu = scan_add(in ? sptx[m] * susr[lane].up : T(0));
-  const T slnext = __shfl_down(sl, 1, WAVE);  // sum over positions > lane
+  const T esl = eu + slnext;
+  const T cl =
+      run_iscan(in ? least_cpu(us.z, skc[lane], Htop - us.up, us.fmin) : T(0), T(0), lg, add);
+  *todo = ok & ~__builtin_amdgcn_ballot_w64(beaten(fma_(rho, ab, esl + cl), inc));
+  if (!*todo) return bmin;
   if (in) {
     Batch<T> r;
     r.lo = lo;
     r.upl = nd;
-    r.esl = eu + ((lane + 1 < n) ? slnext : T(0));
-    r.ab = sA[s] + sB[s] * T(lane + 1);
+    r.esl = esl;
+    r.ab = ab;
     sbt[lane + 1] = r;
+    scl[lane] = cl;
   }
   for (int q = lane; q < WAVE + 1; q += WAVE) {  // past n: infeasible sentinels
     Batch<T> z;
@@ -424,7 +570,7 @@ __device__ int hrow(const HProblem<T> &p, int64_t inst, unsigned char *smem, con
     sbt[n + 1 + q] = z;
   }
   __syncthreads();
-  if (!CONT && ok) {
+  if (!CONT) {
     // Eqs. (1), (2) per (position, level): K4 lanes per user, padding never
     // too slow
     const int upw = WAVE / K4, pk = lane / K4, kk = lane - pk * K4;
@@ -551,31 +697,42 @@ __device__ inline T offload_cpu_energy(const unsigned char *smem, const HLayout 
 }
 
 // Every candidate (s, j, b) of the mode's family for the users in mask (n of
-// them) with the GPU free at tfree: each lane's best (energy, flat index over
-// the n users' family, lowest index among equal energies) in bestE, bestI,
-// and its work in nfeas, nevals when COUNT.  RUN: the users' per-point
-// values come from runs of partition points (HRowCache; the grouping has a
-// table of its own instead).
-template <typename T, bool COUNT, bool GREEDY, bool CONT, int LG = 0, bool RUN = false>
+// them) with the GPU free at tfree that is not beaten by inc, the energy of
+// local computing or +inf, or by a candidate found before: each lane's best
+// (energy, flat index over the n users' family, lowest index among equal
+// energies) in bestE, bestI, and the work of the whole family in nfeas,
+// nevals when COUNT.
+template <typename T, bool COUNT, bool GREEDY, bool CONT, int LG = 0>
 __device__ void hsearch(const HProblem<T> &p, int64_t inst, unsigned char *smem, const HLayout &y,
-                        int lane, uint64_t mask, int n, T tfree, T &bestE, int &bestI, int &nfeas,
-                        int64_t &nevals) {
-  const int K = p.K, J = p.J, s_end = p.s_end, j_low = p.j_low;
+                        int lane, uint64_t mask, int n, T tfree, T inc, T rho, T &bestE,
+                        int &bestI, int &nfeas, int64_t &nevals) {
+  const int N = p.N, K = p.K, J = p.J, s_end = p.s_end, j_low = p.j_low;
   const T *sr = (const T *)(smem + y.r), *sP = (const T *)(smem + y.P);
   const Batch<T> *sbt = (const Batch<T> *)(smem + y.bt);
+  const T *scl = (const T *)(smem + y.gam);
   const int Jn = J - j_low;
   const int Jw = Jn < WAVE ? Jn : WAVE;
   const int nb = WAVE / Jw;
   const int jl = lane % Jw, bo = lane / Jw;
   const bool idle = bo >= nb;  // past the pass's (j, b) pairs: never feasible
+  if (GREEDY && COUNT) inc = inf_of<T>();  // its counters come from the search itself
 
-  HRowCache<T> hc;
-  for (int s = 0; s < s_end; ++s) {
-    bool any;
-    const int bmin =
-        hrow<T, CONT>(p, inst, smem, y, lane, s, tfree, mask, n, &any, false, RUN ? &hc : nullptr);
+  // inc after lanes with `take` found E
+  auto lower_inc = [&](bool take, T E) {
+    if (GREEDY && COUNT) return;
+    if (__builtin_amdgcn_ballot_w64(take & (E < inc))) {
+      const T m = wave_min(take ? E : inf_of<T>());
+      inc = m < inc ? m : inc;
+    }
+  };
+
+  auto search_point = [&](auto by_bounds, int s) {
+    constexpr bool bounds = decltype(by_bounds)::value;
+    uint64_t todo;
+    const int bmin = hrow<T, CONT, COUNT && !GREEDY && !bounds>(
+        p, inst, smem, y, lane, s, tfree, mask, n, inc, rho, &todo, nfeas, nevals);
     const int blo = bmin > 1 ? bmin : 1;
-    if (!any) continue;
+    if (!todo) return;
     const int sJN = s * J * n;
     if (GREEDY) {
       // Alg. 2 at each GPU level (lane = j): the largest set whose users all
@@ -596,51 +753,78 @@ __device__ void hsearch(const HProblem<T> &p, int64_t inst, unsigned char *smem,
         const T Phi = r.ab * rj;
         const T H = r.lo - Phi;
         const bool feas = jok & (bg >= blo) & (H >= tfree);
-        const uint64_t fm = __builtin_amdgcn_ballot_w64(feas);
-        if (fm == 0) continue;
-        const int bw = __builtin_amdgcn_readlane(bg, 63 - __clzll((long long)fm));
-        const T cpu =
-            offload_cpu_energy<T, CONT, LG>(smem, y, K, feas ? H : inf_of<T>(), bg, 0, bw);
-        const T E = fma_(sP[jok ? j : J - 1], Phi, cpu + r.esl);
-        const int idx = sJN + (J - 1 - j) * n + (n - bg);
-        const bool take = feas & better(E, idx, bestE, bestI);
-        bestE = take ? E : bestE;
-        bestI = take ? idx : bestI;
+        const T pj = sP[jok ? j : J - 1];
+        const T lb = fma_(pj, Phi, r.esl + scl[bg > 0 ? bg - 1 : 0]);
+        const bool need = feas & !beaten(lb, inc);
+        const uint64_t fm = __builtin_amdgcn_ballot_w64(need);
         if (COUNT) {
           nfeas += feas ? 1 : 0;
           nevals += feas ? bg : 0;
         }
+        if (fm == 0) continue;
+        const int bw = __builtin_amdgcn_readlane(bg, 63 - __clzll((long long)fm));
+        const T cpu =
+            offload_cpu_energy<T, CONT, LG>(smem, y, K, need ? H : inf_of<T>(), bg, 0, bw);
+        const T E = fma_(pj, Phi, cpu + r.esl);
+        const int idx = sJN + (J - 1 - j) * n + (n - bg);
+        const bool take = need & better(E, idx, bestE, bestI);
+        bestE = take ? E : bestE;
+        bestI = take ? idx : bestI;
+        lower_inc(take, E);
       }
     } else {
-      for (int b0 = blo; b0 <= n; b0 += nb) {
-        bool anyp = false;
+      while (todo) {
+        const int b0 = 1 + __builtin_ctzll(todo);
+        todo = b0 - 1 + nb < WAVE ? todo & (~uint64_t(0) << (b0 - 1 + nb)) : 0;
         for (int jc = 0; jc < Jn; jc += WAVE) {
           const int j = j_low + jc + jl;
           const bool jok = !idle && j < J;
           const int b = b0 + bo;
-          const Batch<T> r = sbt[b0 + bo];
+          const Batch<T> r = sbt[b];
           const T Phi = r.ab * sr[jok ? j : J - 1];            // Eq. (5), layers s+1..L
           const T H = r.lo - Phi;                               // slack to the batch deadline
           const bool feas = jok & (H >= tfree) & (H >= r.upl);  // (6), (7); (8): b >= bmin
-          const uint64_t fm = __builtin_amdgcn_ballot_w64(feas);
+          const T pj = sP[jok ? j : J - 1];
+          const T lb = fma_(pj, Phi, r.esl + scl[b <= n ? b - 1 : 0]);
+          const bool need = feas & !beaten(lb, inc < bestE ? inc : bestE);
+          const uint64_t fm = __builtin_amdgcn_ballot_w64(need);
           if (fm == 0) continue;
-          anyp = true;
           const int bw = b0 + __builtin_amdgcn_readlane(bo, 63 - __clzll((long long)fm));
-          // every feasible lane of the pass has a batch of at least b0
+          // every lane of the pass has a batch of at least b0
           const T cpu =
-              offload_cpu_energy<T, CONT, LG>(smem, y, K, feas ? H : inf_of<T>(), b, b0, bw);
-          const T E = fma_(sP[jok ? j : J - 1], Phi, cpu + r.esl);
+              offload_cpu_energy<T, CONT, LG>(smem, y, K, need ? H : inf_of<T>(), b, b0, bw);
+          const T E = fma_(pj, Phi, cpu + r.esl);
           const int idx = sJN + (J - 1 - j) * n + (n - b);
-          const bool take = feas & better(E, idx, bestE, bestI);
+          const bool take = need & better(E, idx, bestE, bestI);
           bestE = take ? E : bestE;
           bestI = take ? idx : bestI;
-          if (COUNT) {
-            nfeas += feas ? 1 : 0;
-            nevals += feas ? b : 0;
-          }
+          lower_inc(take, E);
         }
-        if (!anyp) break;
       }
+    }
+  };
+
+  // By their bounds, the lowest first, until it is beaten; as they come where
+  // the bounds do not pay: with one or two partition points, and with more
+  // users than let the bounds take several at once (in the greedy search,
+  // whose rows cost less, than four) unless the orders are at hand.  Measured
+  // on the continuous frequency: 25,078 x 17 users 183 us as they come, 130 by
+  // bounds; 6,453 x 47 users, greedy, 208 and 273; 1,769 x 18, greedy, 70 and
+  // 85.
+  if (s_end <= 2 || !(N <= 16 || (!GREEDY && N <= 32) || y.tab >= 0)) {
+    for (int s = 0; s < s_end; ++s) search_point(std::false_type{}, s);
+    return;
+  }
+  T *slb = (T *)(smem + y.cyc);  // (the layers' cycles have been summed)
+  hbounds<T, COUNT && !GREEDY>(p, smem, y, lane, mask, tfree, rho, slb, nfeas, nevals);
+  for (int s0 = 0; s0 < s_end; s0 += WAVE) {
+    T lb = s0 + lane < s_end ? slb[s0 + lane] : inf_of<T>();
+    while (true) {
+      const T m = wave_min(lb);
+      if (!(m < inf_of<T>()) || beaten(m, inc)) break;
+      const int q = __builtin_ctzll(__builtin_amdgcn_ballot_w64(lb == m));
+      lb = lane == q ? inf_of<T>() : lb;
+      search_point(std::true_type{}, s0 + q);
     }
   }
 }
@@ -650,13 +834,13 @@ __device__ void hsearch(const HProblem<T> &p, int64_t inst, unsigned char *smem,
 // (any order).  Both wave-uniform.
 template <typename T>
 __device__ inline bool hlocal(const unsigned char *smem, const HLayout &y, int lane, uint64_t mask,
-                              T *e) {
+                              int n_max, T *e) {
   const int *skL = (const int *)(smem + y.kL);
   const T *seL = (const T *)(smem + y.eL);
   const bool mem = (mask >> lane) & 1;
   const bool ok = __builtin_amdgcn_ballot_w64(mem && skL[lane] < 0) == 0;
   T v = mem ? seL[lane] : T(0);
-  for (int d = 1; d < WAVE; d <<= 1) v = v + __shfl_xor(v, d, WAVE);
+  v = run_reduce(v, n_max <= 16 ? 4 : 6, [](T a, T b) { return a + b; });
   *e = uni(v);
   return ok;
 }
@@ -702,38 +886,33 @@ __device__ void hwinner(const HProblem<T> &p, int64_t inst, unsigned char *smem,
   const int rem = idx - s * (J * n);
   const int j = J - 1 - rem / n;
   const int b = n - (rem - (rem / n) * n);
-  bool any;
-  hrow<T, CONT>(p, inst, smem, y, lane, s, tfree, mask, n, &any, true);
+  horder<T>(p, smem, y, lane, s, mask);
   const T *sC = (const T *)(smem + y.C), *sA = (const T *)(smem + y.A);
   const T *sB = (const T *)(smem + y.B), *slf = (const T *)(smem + y.lf);
-  const T *szet = (const T *)(smem + y.zet), *skap = (const T *)(smem + y.kap);
-  const T *sptx = (const T *)(smem + y.ptx), *srate = (const T *)(smem + y.rate);
+  const T *skap = (const T *)(smem + y.kap), *sptx = (const T *)(smem + y.ptx);
   const T *sr = (const T *)(smem + y.r), *sP = (const T *)(smem + y.P);
-  const int *spi = (const int *)(smem + y.pi);
-  const Batch<T> *sbt = (const Batch<T> *)(smem + y.bt);
+  const T *sdl = (const T *)(smem + y.dl);
+  const bool in = lane < n;  // lane = position in pi_s
+  const int m = in ? ((const int *)(smem + y.pi))[lane] : 0;
+  const HUser<T> us = ((const HUser<T> *)(smem + y.usr))[in ? lane : 0];
   const T Cs = sC[s];
   const T Phi = (sA[s] + sB[s] * T(b)) * sr[j];
-  const T H = sbt[b].lo - Phi;
+  const T H = wave_min(lane < b ? sdl[m] : inf_of<T>()) - Phi;  // lo[b] of Eq. (10)
   T ready = -inf_of<T>();  // the latest offloader, the GPU free time joins below
-  if (mem) {
-    const int m = lane;
-    int pos = 0;
-    for (int q = 0; q < n; ++q) pos += (spi[q] == m) ? q : 0;
+  if (in) {
     int lv;
     int8_t off;
     T fq;
-    if (pos < b) {
-      const T up = ((const T *)(smem + y.bits))[s] / srate[m];
-      const T x = H - up;
-      const T W = szet[m] * Cs;
+    if (lane < b) {
+      const T x = H - us.up;
       const T *f = slf + m * K;
       int k = K - 1;
       for (int q = K - 1; q >= 0; --q)
-        if (W / f[q] <= x) k = q;
-      fq = CONT ? cont_freq(W, x, f[0], f[K - 1]) : f[k];
+        if (us.z / f[q] <= x) k = q;
+      fq = CONT ? cont_freq(us.z, x, f[0], f[K - 1]) : f[k];
       const T e = (skap[m] * (fq * fq)) * Cs;
-      sterm[m] = e + sptx[m] * up;
-      const T done = W / fq + up;
+      sterm[m] = e + sptx[m] * us.up;
+      const T done = us.z / fq + us.up;
       ready = (done > ready) ? done : ready;
       lv = CONT ? -1 : k;
       off = 1;
@@ -762,8 +941,9 @@ __device__ void hwinner(const HProblem<T> &p, int64_t inst, unsigned char *smem,
   __syncthreads();
 }
 
-// Eight waves per SIMD: the rows and the level counts wait on LDS and
-// barriers; 64 registers fit without spills.  LG > 0: level rows of 2^LG
+// Eight waves per SIMD: the rows and the bounds wait on LDS (262,144 x 16
+// users, 22 layers: 1.87 ms at eight waves, 1.92 at seven, 2.00 at six; 5.34
+// before the bounds).  LG > 0: level rows of 2^LG
 // entries (launches without the work counters).
 template <typename T, bool COUNT, bool GREEDY, bool CONT, int LG = 0>
 __global__ __launch_bounds__(WAVE, 8) void jdob_hetero_kernel(HArgs<T> args) {
@@ -780,15 +960,17 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_hetero_kernel(HArgs<T> args) {
   T bestE = inf_of<T>();
   int bestI = 0x7fffffff, nfeas = 0;
   int64_t nevals = 0;
-  // (binary32 with rows of at most 16 levels: otherwise the run's registers
-  // would spill)
-  hsearch<T, COUNT, GREEDY, CONT, LG, (LG <= 4 && sizeof(T) == 4)>(
-      p, inst, smem, y, lane, all, N, tfree, bestE, bestI, nfeas, nevals);
+  const T rho =
+      gpu_energy_rate((const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, J, lane);
+  T eLC;
+  const bool local = hlocal<T>(smem, y, lane, all, N, &eLC);
+  hsearch<T, COUNT, GREEDY, CONT, LG>(
+      p, inst, smem, y, lane, all, N, tfree, local ? eLC : inf_of<T>(), rho, bestE, bestI, nfeas,
+      nevals);
   // local computing competes last
   const int idxLC = L * J * N;
   wave_argmin(bestE, bestI);
-  T eLC;
-  if (hlocal<T>(smem, y, lane, all, &eLC)) {
+  if (local) {
     nfeas += (lane == 0) ? 1 : 0;
     if (better(eLC, idxLC, bestE, bestI)) { bestE = eLC; bestI = idxLC; }
   }
@@ -846,10 +1028,10 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_hetero_kernel(HArgs<T> args) {
 // its members with the GPU free at the previous group's release time.  The
 // dynamic program keeps, per prefix of the deadline order, the front of
 // non-dominated (total energy, GPU release time) states, as the other
-// grouping kernel does.  Six waves per SIMD: with the 76-80 vector and 106
-// scalar registers that allows, nothing spills (at eight waves 20-60 bytes
-// per lane went to scratch and scalar values were kept in vector lanes;
-// measured on h5: 30.9 ms at six waves, 31.2 at seven, 32.3 at eight).
+// grouping kernel does.  Six waves per SIMD: at more, values spill
+// to scratch (16,384 x 10 users, continuous: 5.19 ms at six waves, 5.43 at
+// seven, 5.75 at eight, 5.56 at five; 9.3 before the bounds and the orders
+// kept per partition point).
 template <typename T, bool COUNT, bool GREEDY, bool CONT>
 __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> args) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -866,19 +1048,14 @@ __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> 
   constexpr int F = GROUP_FRONT;
 
   hprepare<T, CONT>(p, inst, smem, y, lane);
-  if (y.pre >= 0 && lane < N) {  // per (s, user), as hrow computes them
-    const T *sC = (const T *)(smem + y.C), *szet = (const T *)(smem + y.zet);
-    const T *slf = (const T *)(smem + y.lf), *srate = (const T *)(smem + y.rate);
-    const T *sbits = (const T *)(smem + y.bits);
-    T *pre = (T *)(smem + y.pre);
+  if (y.tab >= 0) {
+    HPos<T> *tab = (HPos<T> *)(smem + y.tab);
     for (int s = 0; s < p.s_end; ++s) {
-      const T W = szet[lane] * sC[s];
-      const T tK1 = W / slf[lane * p.K + p.K - 1];
-      const T up = sbits[s] / srate[lane];
-      T *q = pre + (s * N + lane) * 3;
-      q[0] = up;
-      q[1] = tK1;
-      q[2] = slack_needed(tK1, up);
+      T g;
+      const HPos<T> u = user_at(smem, y, p.K, s, lane < N ? lane : 0, &g);
+      const int pos = gamma_rank(g, lane < N, N, 6, (uint64_t *)(smem + y.bt), lane);
+      if (lane < N) tab[s * N + pos] = u;
+      __syncthreads();
     }
   }
   if (lane < N) {  // the deadline order
@@ -901,15 +1078,19 @@ __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> 
     const int r = dr[lane < N ? lane : 0];
     return __builtin_amdgcn_ballot_w64(lane < N && r >= lo && r < hi);
   };
+  const T rho =
+      gpu_energy_rate((const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, J, lane);
   // the group's winner among its candidates and local computing, with the
   // GPU free at tf0 (0x7fffffff if none is feasible); counts into nf, ne
   auto group_search = [&](uint64_t mask, int n, T tf0, int &nf, int64_t &ne) -> int {
     T bestE = inf_of<T>();
     int bestI = 0x7fffffff;
-    hsearch<T, COUNT, GREEDY, CONT>(p, inst, smem, y, lane, mask, n, tf0, bestE, bestI, nf, ne);
-    wave_argmin(bestE, bestI);
     T eLC;
-    if (hlocal<T>(smem, y, lane, mask, &eLC)) {
+    const bool local = hlocal<T>(smem, y, lane, mask, N, &eLC);
+    hsearch<T, COUNT, GREEDY, CONT>(p, inst, smem, y, lane, mask, n, tf0,
+                                    local ? eLC : inf_of<T>(), rho, bestE, bestI, nf, ne);
+    wave_argmin(bestE, bestI);
+    if (local) {
       if (COUNT) nf += (lane == 0) ? 1 : 0;
       if (better(eLC, L * J * n, bestE, bestI)) { bestE = eLC; bestI = L * J * n; }
     }

@@ -96,3 +96,37 @@ def test_bounds_joint_takes_upload_times_from_its_tables():
     for k in want:
         if want[k] is not None:
             assert np.array_equal(want[k], got[k]), k
+
+
+# Heterogeneous users: one, two and four partition points' orders at a time
+# (64, 32 and 16 lanes each), fewer partition points than that, and more than
+# 64 of them; both precisions.
+HETERO = [("h1", 96, dict(N=16, L=3, K=8, J=12)), ("h2", 96, dict(N=15, L=66, J=9)),
+          ("h1", 64, dict(N=17, L=21, K=5, J=65)), ("h2", 64, dict(N=32, L=6, J=16)),
+          ("h1", 48, dict(N=33, L=9, K=9, J=7)), ("h2", 32, dict(N=64, L=5, J=33)),
+          ("h2", 96, dict(N=9, L=2, J=64)), ("h1", 64, dict(N=1, L=30, K=4, J=1))]
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2, 4, 8])
+@pytest.mark.parametrize("k", range(len(HETERO)))
+def test_bounds_hetero(k, mode):
+    base, n, kw = HETERO[k]
+    prob = problem(base, n, mode, k % 2 == 0, "f64" if k % 3 == 2 else "f32", 8300 + k, **kw)
+    label = f"bounds {base} {kw} mode={prob['mode']}"
+    print(f"[gpu] {label}", flush=True)
+    ora = oracle.solve(prob, threads=16)
+    for gpu in both(prob, jdob.solve_batch):
+        compare(prob, gpu, ora, label=label)
+
+
+# with the orders kept per partition point, and where they do not fit
+@pytest.mark.parametrize("mode", [0, 1, 4])
+@pytest.mark.parametrize("base,n,kw", [("h5", 48, dict(N=9, L=11, J=12)), ("h1", 16, dict(N=17, L=66, K=5, J=8)),
+                                       ("h1", 24, dict(N=8, L=255, K=3, J=5))])
+def test_bounds_hetero_grouped(base, n, kw, mode):
+    prob = problem(base, n, mode, mode == 1, "f32", 8400, **kw)
+    label = f"bounds grouped {base} {kw} mode={prob['mode']}"
+    print(f"[gpu] {label}", flush=True)
+    ora = oracle.solve_grouped(prob, threads=16)
+    for gpu in both(prob, jdob.solve_grouped):
+        compare_grouped(prob, gpu, ora, label)
