@@ -98,8 +98,9 @@ template <typename T> struct GroupedArgs {
 
 // Byte offsets of the per-instance LDS arrays.
 struct Layout {
-  int cyc, al, be, bits, C, A, B, f, eps, r, P, pi, rate, dl, lo, kL, eL, fL, SL, te, up, bt, term,
-      sflag, q, total;
+  int cyc, al, be, bits, C, A, B, f, eps, r, P, pi, rate, dl, lo, kL, eL, fL, SL, te, up, bt, sflag,
+      q, total;
+  int limit;  // bytes that the limit of one instance's rows counts
 };
 
 // Room of the queue of candidates whose offloaders span several CPU levels
@@ -177,10 +178,10 @@ __host__ __device__ inline Layout make_layout(int N, int L, int K, int J, int sz
   }
   y.sflag = take(L + 1);          // partition point has a feasible candidate
   y.q = take(queue ? QCAP * 4 : 0);  // queued candidates: b | j << 11 | first level << 19
-  // per-user energy of the winner: written after the search has emptied the
-  // queue, so it shares the queue's room where that holds it
-  y.term = (queue && N * szT <= QCAP * 4) ? y.q : take(N * szT);
   y.total = o;
+  // (a row of the winner's per-user energies among them, which has its room
+  // in that of the batch records or of the queue)
+  y.limit = align8(o + ((queue && N * szT <= QCAP * 4) ? 0 : N * szT));
   return y;
 }
 
@@ -487,44 +488,238 @@ __device__ inline int lanes_per_item(int n) {
   return n >= WAVE ? 0 : (n > 1 ? __clz(n - 1) - 26 : 6);
 }
 
-// With local computing feasible, drops the flag of every partition point s
-// whose candidates cannot beat it: each user costs at least the lower of its
-// local energy and that of offloading at the lowest CPU level plus its share
-// rho*B[s] of the batch, on top of rho*A[s].  Lanes take (s, part of the
-// users): two operations per (s, user), against the sort, the scans and the
-// rows that an instance ending here does without (1,048,576 instances of 32
-// users, 22 layers: a flag is left in 3 % of them, of 59 % flagged).
-// Returns whether a flag is left.
+// The rate order pi, the batch deadlines lo[b] (Eq. (10)), the rates in pi
+// order and the local-energy suffix sums SL (ranking only) that the search
+// reads.
 template <typename T>
-__device__ inline bool drop_beaten(const Problem<T> &p, unsigned char *smem, const Layout &y,
+__device__ inline void order_users(const Problem<T> &p, unsigned char *smem, const Layout &y,
                                    int lane) {
   const int N = p.N;
-  const T *sC = (const T *)(smem + y.C), *sA = (const T *)(smem + y.A);
-  const T *sB = (const T *)(smem + y.B), *seps = (const T *)(smem + y.eps);
-  const T *seL = (const T *)(smem + y.eL);
-  int8_t *sflag = (int8_t *)(smem + y.sflag);
-  const T rho = gpu_energy_rate((const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, p.J, lane);
-  T lc = T(0);
-  for (int m = lane; m < N; m += WAVE) lc = lc + seL[m];
-  lc = lane_read(wave_iscan(lc, T(0), [](T a, T b) { return a + b; }), WAVE - 1);
-  const int lg = lanes_per_item(p.s_end), parts = 1 << lg, part = lane & (parts - 1);
-  bool left = false;
-  for (int s0 = 0; s0 < p.s_end; s0 += WAVE >> lg) {
-    const int s = s0 + (lane >> lg);
-    const int sc = s < p.s_end ? s : 0;
-    const T off = fma_(rho, sB[sc], seps[0] * sC[sc]);
-    T acc = T(0);
-    for (int m = part; m < N; m += parts) {
-      const T e = seL[m];
-      acc = acc + (e < off ? e : off);
+  int16_t *spi = (int16_t *)(smem + y.pi);
+  T *srate = (T *)(smem + y.rate), *slo = (T *)(smem + y.lo), *sup = (T *)(smem + y.up);
+  const T *sdl = (const T *)(smem + y.dl), *seL = (const T *)(smem + y.eL);
+  T *sSL = (T *)(smem + y.SL);
+  for (int i = lane; i < N; i += WAVE) spi[i] = i;  // stays a permutation of valid users
+  __syncthreads();
+  rank_users(srate, (uint64_t *)(smem + y.bt), spi, N, lane);
+  __syncthreads();
+  {
+    T carry = inf_of<T>();
+    for (int i0 = 0; i0 < N; i0 += WAVE) {
+      const int i = i0 + lane;
+      if (i < N) sup[i] = srate[spi[i]];
+      const T d = (i < N) ? sdl[spi[i]] : inf_of<T>();
+      T v = wave_scan<T, true>(d, lane);
+      v = (carry < v) ? carry : v;
+      if (i < N) slo[i + 1] = v;
+      carry = lane_read(v, WAVE - 1);
     }
-    acc = run_reduce(acc, lg, [](T a, T b) { return a + b; });
-    if (s < p.s_end) {
-      if (beaten(fma_(rho, sA[sc], acc), lc)) sflag[s] = 0;  // (its lanes agree)
-      left |= sflag[s] != 0;
-    }
+    if (lane == 0) slo[0] = inf_of<T>();
+    __syncthreads();
+    for (int i = lane; i < N; i += WAVE) srate[i] = sup[i];
   }
-  return __builtin_amdgcn_ballot_w64(left) != 0;
+  {
+    T carry = T(0);
+    for (int i0 = ((N - 1) / WAVE) * WAVE; i0 >= 0; i0 -= WAVE) {
+      // reversed inclusive scan inside the chunk: lane q holds pi index
+      // i0 + WAVE - 1 - q
+      const int i = i0 + WAVE - 1 - lane;
+      T v = (i < N) ? seL[spi[i]] : T(0);
+      v = wave_scan<T, false>(v, lane) + carry;
+      if (i < N) sSL[i] = v;
+      carry = lane_read(v, WAVE - 1);
+    }
+    if (lane == 0) sSL[N] = T(0);
+  }
+  __syncthreads();
+}
+
+// With local computing feasible (energy lc), whether partition point s cannot
+// beat it: each user costs at least the lower of its local energy and that of
+// offloading at the lowest CPU level plus its share rho*B[s] of the batch, on
+// top of rho*A[s].  quads: the users' local energies, zero up to a multiple of
+// four; each run of 2^lg lanes holds one partition point and shares the
+// users.  Two operations per (s, user), against the sort, the scans and the
+// rows that an instance ending here does without (1,048,576 instances of 32
+// users, 22 layers: a partition point is left in 3 % of them, of 59 % with a
+// feasible candidate).
+template <typename T>
+__device__ inline bool beaten_by_local(T C, T A, T B, T eps0, T rho, T lc, const T *quads, int N,
+                                       int lg, int lane) {
+  const T off = fma_(rho, B, eps0 * C);
+  T acc = T(0);
+  for (int m = 4 * (lane & ((1 << lg) - 1)); m < N; m += 4 << lg) {
+    const Quad<T> e = *(const Quad<T> *)(quads + m);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc = acc + (e.v[c] < off ? e.v[c] : off);
+  }
+  acc = run_reduce(acc, lg, [](T a, T b) { return a + b; });
+  return beaten(fma_(rho, A, acc), lc);
+}
+
+// The preparation for up to 64 users, GPU levels and CPU levels and fewer than
+// 64 layers, one per lane: the rows are loaded together and kept in registers,
+// the sums run along the lanes, and with local computing feasible the
+// partition points that cannot beat it drop out before anything else is
+// computed.  (1,048,576 instances of 32 users, 22 layers, most of which end
+// there: 1.57 -> 1.02 ms; 200,003 of them, greedy, 298 -> 202 us; 4,096 of 8
+// users, 16 layers, where one wave's latency is the time, 22.3 -> 19.5 us.)
+template <typename T, bool CONT, bool KEEP>
+__device__ bool prepare_lanes(const Problem<T> &p, int64_t inst, unsigned char *smem,
+                              const Layout &y, int lane, T tfree, int &bmin_out) {
+  const int N = p.N, L = p.L, K = p.K, J = p.J;
+  T *sC = (T *)(smem + y.C), *sA = (T *)(smem + y.A), *sB = (T *)(smem + y.B);
+  T *sf = (T *)(smem + y.f), *seps = (T *)(smem + y.eps);
+  T *sr = (T *)(smem + y.r), *sP = (T *)(smem + y.P);
+  T *srate = (T *)(smem + y.rate), *sdl = (T *)(smem + y.dl);
+  int8_t *skL = (int8_t *)(smem + y.kL), *sflag = (int8_t *)(smem + y.sflag);
+  T *seL = (T *)(smem + y.eL), *sSL = (T *)(smem + y.SL), *sfL = (T *)(smem + y.fL);
+  Level<T> *ste = (Level<T> *)(smem + y.te);
+  T *sbits = (T *)(smem + y.bits);
+  T *quads = (T *)(smem + y.bt);
+  auto add = [](T a, T b) { return a + b; };
+
+  // 1. the rows (lanes past a row's end repeat its last entry, or zero)
+  const bool isl = lane < L, ism = lane < N;
+  const int lc_ = isl ? lane : L - 1, mc = ism ? lane : N - 1;
+  const T f = p.lf[lane < K ? lane : K - 1], g = p.gf[lane < J ? lane : J - 1];
+  const T xc = p.cyc[inst * L + lc_], xa = p.alpha[inst * L + (L - 1 - lc_)];
+  const T xb = p.beta[inst * L + (L - 1 - lc_)];
+  const T rate = p.rate[inst * N + mc], Tm = p.deadline[inst * N + mc];
+  const T bits = p.bits[inst * (L + 1) + (lane <= L ? lane : L)];
+  const T f0 = lane_read(f, 0), ftop = lane_read(f, K - 1), gtop = lane_read(g, J - 1);
+  // the sums C, A, B in the sequential order of the contract (lane i of the
+  // second and third holds layer L - i on)
+  T c = isl ? xc : T(0), a = isl ? xa : T(0), b = isl ? xb : T(0);
+  lane_chains(c, a, b, L);
+  if (isl) {
+    sC[lane + 1] = c;
+    sA[L - 1 - lane] = a;
+    sB[L - 1 - lane] = b;
+  }
+  if (lane == 0) {
+    sC[0] = T(0);
+    sA[L] = T(0);
+    sB[L] = T(0);
+  }
+  // local computing of the whole chain: each user's lowest level meeting
+  // its deadline (latency falls with the level: binary search for the
+  // number of levels that are too slow)
+  const T CL = lane_read(c, L - 1), eps = p.kappa * (f * f);
+  const T tL = CL / f;
+  if (lane < K) {
+    ste[lane].t = tL;
+    ste[lane].e = eps * CL;
+    sf[lane] = f;
+  }
+  __syncthreads();
+  int kc = 0;
+  for (int step = K > 1 ? 1 << (31 - __clz(K - 1)) : 0; step > 0; step >>= 1) {
+    const int nc = kc + step;
+    kc = (nc <= K && ste[nc <= K ? nc - 1 : 0].t > Tm) ? nc : kc;
+  }
+  const bool has = kc < K && ste[kc < K ? kc : 0].t <= Tm;
+  const int kL = has ? kc : -1;
+  T eL = has ? ste[kc < K ? kc : 0].e : inf_of<T>();
+  if (CONT) {  // Eq. (20) with its clamp against the user's deadline
+    T fL = T(0);
+    if (has) {
+      fL = cont_freq(CL, Tm, f0, ftop);
+      eL = (p.kappa * (fL * fL)) * CL;
+    }
+    if (ism) sfL[lane] = fL;
+  }
+  if (ism) {
+    skL[lane] = (int8_t)kL;
+    seL[lane] = eL;
+  }
+  const uint64_t bad = __builtin_amdgcn_ballot_w64(ism && !has);
+  // GPU power at level `lane`, and the stretch of its latency
+  const T P = p.gc * ((g * g) * g) + p.p0;
+
+  // 2. local computing feasible: drop what cannot beat it
+  uint64_t cand = ~uint64_t(0);  // partition points, bit s
+  if (!KEEP && bad == 0) {
+    T rho = inf_of<T>();
+    if (lane >= p.j_low && lane < J) rho = P * (gtop * rough_rcp(g));
+    rho = wave_min(rho) * T(1.0 - 0x1p-20);
+    const T lc = lane_read(run_reduce(ism ? eL : T(0), 6, add), 0);
+    quads[lane] = ism ? eL : T(0);
+    __syncthreads();
+    const int lg = lanes_per_item(p.s_end), s = lane >> lg;
+    const int sc = s < p.s_end ? s : 0;
+    const bool drop = beaten_by_local(sC[sc], sA[sc], sB[sc], p.kappa * (f0 * f0), rho, lc, quads,
+                                      N, lg, lane);
+    // (the lanes of a partition point agree: the first one's bit)
+    const uint64_t keep = __builtin_amdgcn_ballot_w64(s < p.s_end && !drop);
+    bmin_out = 0;
+    if (keep == 0) {
+      if (lane == 0) sSL[0] = lc;
+      __syncthreads();
+      return false;
+    }
+    if (lg > 0) {  // gather every 2^lg-th bit: lane s asks for bit s << lg
+      cand = __builtin_amdgcn_ballot_w64(lane < (WAVE >> lg) && ((keep >> ((lane << lg) & 63)) & 1));
+    } else {
+      cand = keep;
+    }
+    __syncthreads();
+  }
+
+  // 3. bmin and the blo-th user of pi without sorting (pi orders users by rate
+  // descending, ties by lower index).  The last user of pi without a local
+  // level has the lowest rate among them, then the highest index.
+  int bmin = 0, ub;
+  T rb, lob;
+  if (bad) {
+    const bool mine = ism && !has;
+    rb = wave_min(mine ? rate : inf_of<T>());
+    const uint64_t at = __builtin_amdgcn_ballot_w64(mine && rate == rb);
+    ub = at ? 63 - __clzll((long long)at) : 0;  // (none only with rates outside the contract)
+    const bool ahead = ism && (rate > rb || (rate == rb && lane <= ub));
+    bmin = __popcll(__builtin_amdgcn_ballot_w64(ahead));
+    lob = wave_min(ahead ? Tm : inf_of<T>());
+  } else {
+    rb = wave_max(ism ? rate : -inf_of<T>());
+    const uint64_t at = __builtin_amdgcn_ballot_w64(ism && rate == rb);
+    ub = at ? __builtin_ctzll(at) : 0;
+    lob = lane_read(Tm, ub);
+  }
+  bmin_out = bmin;
+  const int blo = bmin > 1 ? bmin : 1;
+
+  // 4. the test of every partition point left at the top GPU level (where the
+  // stretch is 1) and blo
+  const int s = lane < p.s_end ? lane : 0;
+  const T tK1 = lane_before(c) / ftop;  // C[s] over the top CPU level
+  const T upl = bits / rb;
+  const T Phi = sA[s] + sB[s] * T(blo);
+  const T H = lob - Phi;
+  const bool ok = lane < p.s_end && ((cand >> lane) & 1) && (H >= tfree) && (tK1 <= H - upl);
+  if (lane < p.s_end) sflag[lane] = ok;
+  if (!__builtin_amdgcn_ballot_w64(ok)) {
+    if (bmin == 0) {  // local computing is the only candidate: its ranking energy
+      const T lc = lane_read(run_reduce(ism ? eL : T(0), 6, add), 0);
+      if (lane == 0) sSL[0] = lc;
+    }
+    __syncthreads();
+    return false;
+  }
+
+  // 5. what the search reads
+  if (lane < K) seps[lane] = eps;
+  if (lane < J) {
+    sr[lane] = gtop / g;
+    sP[lane] = P;
+  }
+  if (lane <= L) sbits[lane] = bits;
+  if (ism) {
+    srate[lane] = rate;
+    sdl[lane] = Tm;
+  }
+  __syncthreads();
+  order_users(p, smem, y, lane);
+  return true;
 }
 
 // Preparation of the fused solve.  Every step is exact (orders, minima and
@@ -544,23 +739,23 @@ __device__ inline bool drop_beaten(const Problem<T> &p, unsigned char *smem, con
 //      sums SL that the search reads.
 //   (unless KEEP) when local computing is feasible, the passing partition
 //   points whose energy bound exceeds its energy are dropped first (see
-//   drop_beaten): most instances where it wins end here, unsorted.
+//   beaten_by_local): most instances where it wins end here, unsorted.
 // Returns whether some partition point is left; bmin_out receives bmin.
 template <typename T, bool CONT, bool KEEP>
 __device__ bool prepare_fused(const Problem<T> &p, int64_t inst, unsigned char *smem,
                               const Layout &y, int lane, T tfree, int &bmin_out) {
   const int N = p.N, L = p.L, K = p.K, J = p.J;
+  if (N <= WAVE && L < WAVE && K <= WAVE && J <= WAVE)
+    return prepare_lanes<T, CONT, KEEP>(p, inst, smem, y, lane, tfree, bmin_out);
   T *sC = (T *)(smem + y.C), *sA = (T *)(smem + y.A), *sB = (T *)(smem + y.B);
   T *sf = (T *)(smem + y.f), *seps = (T *)(smem + y.eps);
   T *sr = (T *)(smem + y.r), *sP = (T *)(smem + y.P);
-  int16_t *spi = (int16_t *)(smem + y.pi);
-  T *srate = (T *)(smem + y.rate), *sdl = (T *)(smem + y.dl), *slo = (T *)(smem + y.lo);
+  T *srate = (T *)(smem + y.rate), *sdl = (T *)(smem + y.dl);
   int8_t *skL = (int8_t *)(smem + y.kL);
   T *seL = (T *)(smem + y.eL), *sSL = (T *)(smem + y.SL), *sfL = (T *)(smem + y.fL);
   Level<T> *ste = (Level<T> *)(smem + y.te);
   T *scyc = (T *)(smem + y.cyc), *sal = (T *)(smem + y.al), *sbe = (T *)(smem + y.be);
   T *sbits = (T *)(smem + y.bits);
-  T *sup = (T *)(smem + y.up);
   int8_t *sflag = (int8_t *)(smem + y.sflag);
 
   // 1. level tables (Eqs. (1), (2), (5)) and the instance rows (coalesced)
@@ -704,8 +899,23 @@ __device__ bool prepare_fused(const Problem<T> &p, int64_t inst, unsigned char *
   bmin_out = bmin;
   bool left = __builtin_amdgcn_ballot_w64(any != 0) != 0;
   if (!KEEP && left && bmin == 0) {
-    __syncthreads();  // the flags and local energies, read by other lanes
-    left = drop_beaten(p, smem, y, lane);
+    const T rho = gpu_energy_rate(sr, sP, p.j_low, J, lane);
+    T *quads = (T *)(smem + y.bt);  // zero up to a multiple of four (bt holds 4 (N + 2) and more)
+    T lc = T(0);
+    for (int m = lane; m < N; m += WAVE) lc = lc + seL[m];
+    lc = lane_read(run_reduce(lc, 6, [](T a, T b) { return a + b; }), 0);
+    for (int m = lane; m < ((N + 3) & ~3); m += WAVE) quads[m] = m < N ? seL[m] : T(0);
+    __syncthreads();
+    const int lg = lanes_per_item(p.s_end);
+    left = false;
+    for (int s0 = 0; s0 < p.s_end; s0 += WAVE >> lg) {
+      const int s = s0 + (lane >> lg), sc = s < p.s_end ? s : 0;
+      if (beaten_by_local(sC[sc], sA[sc], sB[sc], seps[0], rho, lc, quads, N, lg, lane) &&
+          s < p.s_end)
+        sflag[s] = 0;  // (the lanes of a partition point agree)
+      left |= s < p.s_end && sflag[s] != 0;
+    }
+    left = __builtin_amdgcn_ballot_w64(left) != 0;
   }
   if (!left) {
     if (bmin == 0) {  // local computing is the only candidate: its ranking energy
@@ -718,41 +928,7 @@ __device__ bool prepare_fused(const Problem<T> &p, int64_t inst, unsigned char *
     return false;
   }
 
-  // 4. the rate order, batch deadlines (Eq. (10)), rates in pi order and
-  // the local-energy suffix sums (ranking only)
-  for (int i = lane; i < N; i += WAVE) spi[i] = i;  // stays a permutation of valid users
-  __syncthreads();
-  rank_users(srate, (uint64_t *)(smem + y.bt), spi, N, lane);
-  __syncthreads();
-  {
-    T carry = inf_of<T>();
-    for (int i0 = 0; i0 < N; i0 += WAVE) {
-      const int i = i0 + lane;
-      if (i < N) sup[i] = srate[spi[i]];
-      const T d = (i < N) ? sdl[spi[i]] : inf_of<T>();
-      T v = wave_scan<T, true>(d, lane);
-      v = (carry < v) ? carry : v;
-      if (i < N) slo[i + 1] = v;
-      carry = lane_read(v, WAVE - 1);
-    }
-    if (lane == 0) slo[0] = inf_of<T>();
-    __syncthreads();
-    for (int i = lane; i < N; i += WAVE) srate[i] = sup[i];
-  }
-  {
-    T carry = T(0);
-    for (int i0 = ((N - 1) / WAVE) * WAVE; i0 >= 0; i0 -= WAVE) {
-      // reversed inclusive scan inside the chunk: lane q holds pi index
-      // i0 + WAVE - 1 - q
-      const int i = i0 + WAVE - 1 - lane;
-      T v = (i < N) ? seL[spi[i]] : T(0);
-      v = wave_scan<T, false>(v, lane) + carry;
-      if (i < N) sSL[i] = v;
-      carry = lane_read(v, WAVE - 1);
-    }
-    if (lane == 0) sSL[N] = T(0);
-  }
-  __syncthreads();
+  order_users(p, smem, y, lane);
   return true;
 }
 
@@ -817,6 +993,18 @@ __device__ inline T cont_sum_f2(const T *sup, T Hu, int b, int b_all, int bw, T 
   for (; g < bw; ++g) {
     const T fr = clamp_(Cs * fast_rcp(Hu - sup[g]), fmin, fmax);
     acc = (g < b) ? fma_(fr, fr, acc) : acc;
+  }
+  return acc;
+}
+
+// The sum of N non-negative terms in order (Eq. (21)), zero up to a multiple of
+// four on a 16-byte boundary; every lane gets it.
+template <typename T> __device__ inline T sum_in_order(const T *terms, int N) {
+  T acc = T(0);
+  for (int m = 0; m < N; m += 4) {
+    const Quad<T> q = *(const Quad<T> *)(terms + m);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc = acc + q.v[c];
   }
   return acc;
 }
@@ -1503,7 +1691,7 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_solve_kernel(SolveArgs<T> args) 
   int8_t *skL = (int8_t *)(smem + y.kL);
   T *seL = (T *)(smem + y.eL), *sSL = (T *)(smem + y.SL);
   Level<T> *ste = (Level<T> *)(smem + y.te);
-  T *sterm = (T *)(smem + y.term);
+  T *sterm = (T *)(smem + y.bt);  // (the rows are no longer read)
 
   const int blo = uni(bmin > 1 ? bmin : 1);  // smallest admissible batch
   T bestE = inf_of<T>();
@@ -1521,15 +1709,15 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_solve_kernel(SolveArgs<T> args) 
     nfeas += (lane == 0) ? 1 : 0;
     if (better(sSL[0], idxLC, bestE, bestI)) { bestE = sSL[0]; bestI = idxLC; }
   }
-  const int64_t totfeas = wave_sum_i64((int64_t)nfeas);
-  const int64_t totev = wave_sum_i64((int64_t)nevals);
-
   const Policy<T> out = output_pointers<T>();
   int8_t *ul = out.ulevel + inst * N;
   int8_t *uo = out.uoffload + inst * N;
-  if (lane == 0) {
-    if (out.nfeas) out.nfeas[inst] = (int32_t)totfeas;
-    if (out.nevals) out.nevals[inst] = totev;
+  if constexpr (COUNT) {
+    const int64_t totfeas = wave_sum_i64(nfeas), totev = wave_sum_i64(nevals);
+    if (lane == 0) {
+      if (out.nfeas) out.nfeas[inst] = (int32_t)totfeas;
+      if (out.nevals) out.nevals[inst] = totev;
+    }
   }
   if (bestI == 0x7fffffff) {  // nothing feasible
     if (lane == 0) {
@@ -1556,9 +1744,10 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_solve_kernel(SolveArgs<T> args) 
     }
     if (T *uf = freq_row<T>(inst, N))
       for (int m = lane; m < N; m += WAVE) uf[m] = local_freq<T, CONT>(smem, y, m);
+    for (int m = lane; m < ((N + 3) & ~3); m += WAVE) sterm[m] = m < N ? seL[m] : T(0);
+    __syncthreads();
+    const T acc = sum_in_order(sterm, N);
     if (lane == 0) {
-      T acc = T(0);
-      for (int m = 0; m < N; ++m) acc = acc + seL[m];
       out.status[inst] = 0;
       out.cut[inst] = L;
       out.gpu_level[inst] = -1;
@@ -1605,14 +1794,13 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_solve_kernel(SolveArgs<T> args) 
       sterm[m] = seL[m];
     }
   }
+  for (int m = N + lane; m < ((N + 3) & ~3); m += WAVE) sterm[m] = T(0);
   ready = wave_max(ready);
   __syncthreads();
   if (T *uf = freq_row<T>(inst, N))
     for (int m = lane; m < N; m += WAVE) uf[m] = sfq[m];
+  const T acc = sum_in_order(sterm, N) + sP[j] * Phi;
   if (lane == 0) {
-    T acc = T(0);
-    for (int m = 0; m < N; ++m) acc = acc + sterm[m];
-    acc = acc + sP[j] * Phi;
     out.status[inst] = 0;
     out.cut[inst] = s;
     out.gpu_level[inst] = j;
@@ -1721,10 +1909,13 @@ __device__ inline void group_winner(const Problem<T> &p, int64_t inst, unsigned 
   const int8_t *skL = (const int8_t *)(smem + y.kL);
   const T *seL = (const T *)(smem + y.eL);
   Level<T> *ste = (Level<T> *)(smem + y.te);
-  T *sterm = (T *)(smem + y.term);
+  T *sterm = (T *)(smem + y.bt);  // (the rows are no longer read)
   const int *dr = (const int *)(smem + gy.drank);
   const size_t o = (size_t)inst * N;
-  T acc = T(0), gpu = T(0), ready = tfree;
+  T ready = tfree;
+  // (the others' terms are zero: adding them changes nothing)
+  for (int m = lane; m < ((N + 3) & ~3); m += WAVE) sterm[m] = T(0);
+  __syncthreads();
   if (idx == L * J * g) {  // local computing
     for (int m = lane; m < N; m += WAVE) {
       if (dr[m] < j || dr[m] >= i) continue;
@@ -1737,10 +1928,7 @@ __device__ inline void group_winner(const Problem<T> &p, int64_t inst, unsigned 
       }
     }
     __syncthreads();
-    if (lane == 0)
-      for (int m = 0; m < N; ++m)
-        if (dr[m] >= j && dr[m] < i) acc = acc + sterm[m];
-    E = lane_read(acc, 0);
+    E = sum_in_order(sterm, N);
     tf = tfree;
     if (slack) *slack = inf_of<T>();
     if (rdy) *rdy = -inf_of<T>();
@@ -1790,12 +1978,7 @@ __device__ inline void group_winner(const Problem<T> &p, int64_t inst, unsigned 
   }
   ready = wave_max(ready);
   __syncthreads();
-  if (lane == 0) {
-    for (int m = 0; m < N; ++m)
-      if (dr[m] >= j && dr[m] < i) acc = acc + sterm[m];
-    gpu = acc + sP[jg] * Phi;
-  }
-  E = lane_read(gpu, 0);
+  E = sum_in_order(sterm, N) + sP[jg] * Phi;
   tf = ((tfree > ready) ? tfree : ready) + Phi;
   if (slack) *slack = H;
   if (rdy) *rdy = ready;
@@ -1875,6 +2058,7 @@ __global__ __launch_bounds__(WAVE, 7) void jdob_grouped_kernel(GroupedArgs<T> ar
   };
 
   int nfeas = 0, nevals = 0, ninner = 0;
+  int64_t nfeas_all = 0, nevals_all = 0;
   for (int i = 1; i <= N; ++i) {
     int ni = 0;  // states in the front of prefix i
     for (int j = 0; j < i; ++j) {  // last group: ord[j..i-1]
@@ -1908,6 +2092,11 @@ __global__ __launch_bounds__(WAVE, 7) void jdob_grouped_kernel(GroupedArgs<T> ar
           tk = k >= 0 ? uni(fT[j * F + k]) : tk;
         } while (k >= 0 && H >= tk);
       }
+      if constexpr (COUNT) {  // (a lane's sums over one group stay below 2^31)
+        nfeas_all += wave_sum_i64(nfeas);
+        nevals_all += wave_sum_i64(nevals);
+        nfeas = nevals = 0;
+      }
     }
     if (lane == 0) fn[i] = ni;
     __syncthreads();
@@ -1928,12 +2117,12 @@ __global__ __launch_bounds__(WAVE, 7) void jdob_grouped_kernel(GroupedArgs<T> ar
     out.ugroup[o + q] = -1;
     if (out.ufreq) out.ufreq[o + q] = T(0);
   }
-  const int64_t totfeas = wave_sum_i64((int64_t)nfeas);
-  const int64_t totev = wave_sum_i64((int64_t)nevals);
-  if (lane == 0) {
-    if (out.ninner) out.ninner[inst] = ninner;
-    if (out.nfeas) out.nfeas[inst] = totfeas;
-    if (out.nevals) out.nevals[inst] = totev;
+  if constexpr (COUNT) {
+    if (lane == 0) {
+      if (out.ninner) out.ninner[inst] = ninner;
+      if (out.nfeas) out.nfeas[inst] = nfeas_all;
+      if (out.nevals) out.nevals[inst] = nevals_all;
+    }
   }
   if (uni(fn[N]) == 0) {
     if (lane == 0) {
@@ -2422,7 +2611,7 @@ int validate(const jdob_problem *p) {
   const bool greedy = (p->mode & JDOB_MODE_GREEDY) != 0;
   if (make_layout(p->num_users, p->num_layers, p->num_local_levels, p->num_gpu_levels, sz, cont,
                   queued_search(p->num_users, cont, greedy), sentinels_of(p))
-          .total > LDS_LIMIT)
+          .limit > LDS_LIMIT)
     return JDOB_ERR_UNSUPPORTED;
   return JDOB_OK;
 }
@@ -2750,7 +2939,8 @@ int jdob_solve_grouped(const jdob_problem *p, jdob_grouped_policy *out, void *hi
   const Layout y = make_layout(p->num_users, p->num_layers, p->num_local_levels,
                                p->num_gpu_levels, sz, (p->mode & JDOB_MODE_CONTINUOUS_CPU) != 0,
                                false, sentinels_of(p));
-  if (make_glayout(y, p->num_users, sz).total > LDS_LIMIT) return JDOB_ERR_UNSUPPORTED;
+  if (make_glayout(y, p->num_users, sz).total + (y.limit - y.total) > LDS_LIMIT)
+    return JDOB_ERR_UNSUPPORTED;
   if (p->num_instances == 0) return JDOB_OK;
   if (!grouped_ok(out)) return JDOB_ERR_INVALID_ARG;
   hipStream_t s = (hipStream_t)hip_stream;

@@ -100,20 +100,6 @@ __device__ inline bool better(T e1, int i1, T e2, int i2) {
   return (e1 < e2) || (e1 == e2 && i1 < i2);
 }
 
-// The outer grouping ranks a group ending the deadline order at i by the
-// total dpE + E with E the exact (canonically summed) energy of the group's
-// winner, which takes a recomputation of that winner.  Its ranking energy Er
-// sums the same non-negative terms in another order and grouping (scans,
-// runs of equal level, a fused GPU term; with a continuous frequency a
-// hardware reciprocal good to an ulp or two): at most about a hundred
-// roundings of 2^-24 each in binary32, so Er and E differ by less than 1e-5
-// of either.  Rounded addition is monotone, so a total that exceeds the best
-// one so far with Er lowered by 1e-4 exceeds it exactly as well: the group
-// can neither win nor tie, and its recomputation is skipped.
-template <typename T> __device__ inline bool cannot_win(T dpE, T Er, T best) {
-  return dpE + Er * T(0.9999) > best;
-}
-
 // Lane moves by DPP (data-parallel primitives of the VALU, no LDS round
 // trip): row_shr:n inside each row of 16 lanes, row_bcast:15 and
 // row_bcast:31 across rows.  Lanes without a source, and rows outside
@@ -168,6 +154,31 @@ template <typename V, typename OP> __device__ inline V run_reduce(V v, int lg, O
   return v;
 }
 
+// The lane before's value, zero in lane 0 (DPP wave_shr:1).
+__device__ inline float lane_before(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ inline double lane_before(double v) {
+  const long long q = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(q & 0xffffffff), 0x138, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(q >> 32), 0x138, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Three chains of L <= 64 terms, one term per lane (zero past the last), as
+// running sums in lane order: run[l] = run[l-1] + x[l], the additions of a
+// sequential sum.  Lane l is final after l steps and stays so.  One addition
+// per step and chain, no LDS (the LDS form, chain_sums, takes 1,500 cycles at
+// L = 16, this one 500).
+template <typename T> __device__ inline void lane_chains(T &a, T &b, T &c, int L) {
+  const T x = a, y = b, z = c;
+  for (int l = 1; l < L; ++l) {
+    a = lane_before(a) + x;
+    b = lane_before(b) + y;
+    c = lane_before(c) + z;
+  }
+}
+
 // Lowest (energy, index) of the wave, lexicographically; every lane gets it.
 template <typename T>
 __device__ inline void wave_argmin(T &e, int &idx) {
@@ -195,10 +206,12 @@ __device__ inline int wave_max_int(int v) {
   return lane_read(v, WAVE - 1);
 }
 
-__device__ inline int64_t wave_sum_i64(int64_t v) {
-#pragma unroll
-  for (int d = 1; d < WAVE; d <<= 1) v += __shfl_xor(v, d, WAVE);
-  return v;
+// Sum over the wave of non-negative values below 2^31.
+__device__ inline int64_t wave_sum_i64(int v) {
+  auto add = [](int a, int b) { return a + b; };
+  const int lo = lane_read(wave_iscan(v & 0xffff, 0, add), WAVE - 1);
+  const int hi = lane_read(wave_iscan(v >> 16, 0, add), WAVE - 1);
+  return ((int64_t)hi << 16) + lo;
 }
 
 // Wave-wide minimum and maximum (every lane gets the value).

@@ -103,14 +103,19 @@ struct HLayout {
   int drank, dord, fE, fT, from, fn, ends, eks;  // the grouping program
   int tab;                                        // the grouping's orders, -1: none
   int K4, total;
+  int limit;  // bytes that the limit of one instance's rows counts
 };
 
 __host__ __device__ inline HLayout make_hlayout(int N, int L, int K, int J, int szT,
                                                bool grouped) {
   HLayout y;
-  int o = 0;
-  auto take = [&](int bytes) { int r = o; o = align8(o + bytes); return r; };
-  auto take32 = [&](int bytes) { o = (o + 31) & ~31; int r = o; o = align8(o + bytes); return r; };
+  int o = 0, lim = 0;  // (the limit also counts a row of rank keys)
+  auto take = [&](int bytes) { int r = o; o = align8(o + bytes); lim = align8(lim + bytes); return r; };
+  auto take32 = [&](int bytes) {
+    o = (o + 31) & ~31;
+    lim = (lim + 31) & ~31;
+    return take(bytes);
+  };
   y.K4 = 4;
   while (y.K4 < K) y.K4 <<= 1;  // level row stride: a power of two, pads never too slow
   y.cyc = take(L * szT);
@@ -132,6 +137,7 @@ __host__ __device__ inline HLayout make_hlayout(int N, int L, int K, int J, int 
   y.eL = take(N * szT);
   y.fL = take(N * szT);
   y.gam = take(N * szT);                       // bound of the first b users' CPU energy
+  lim = align8(((lim + 31) & ~31) + ((N + 1) & ~1) * 8);
   y.need = take(N * szT);
   y.pi = take(N * 4);
   y.usr = take32((N + 1) * 4 * szT);           // HUser by position (+1: read-ahead)
@@ -158,6 +164,7 @@ __host__ __device__ inline HLayout make_hlayout(int N, int L, int K, int J, int 
   // kept per partition point where the table costs no occupancy (the
   // workgroups that fit a CU's LDS, at most 24 of one wave each) and stays
   // within the limit of one workgroup.
+  y.limit = lim;
   y.tab = -1;
   const int base = (o + 31) & ~31, tab_bytes = L * N * 4 * szT;
   auto per_cu = [](int bytes) { const int w = LDS_PER_CU / (bytes > 0 ? bytes : 1); return w < 24 ? w : 24; };
@@ -418,7 +425,7 @@ __device__ inline int feasible_levels(const HProblem<T> &p, const T *sr, T lo, T
 // Counts the feasible candidates into nfeas, nevals when COUNT.
 template <typename T, bool COUNT>
 __device__ void hbounds(const HProblem<T> &p, unsigned char *smem, const HLayout &y, int lane,
-                        uint64_t mask, T tfree, T rho, T *slb, int &nfeas, int64_t &nevals) {
+                        uint64_t mask, T tfree, T rho, T *slb, int &nfeas, int &nevals) {
   const int N = p.N, K = p.K, J = p.J;
   const T *sC = (const T *)(smem + y.C), *sA = (const T *)(smem + y.A);
   const T *sB = (const T *)(smem + y.B), *sr = (const T *)(smem + y.r);
@@ -494,7 +501,7 @@ __device__ void hbounds(const HProblem<T> &p, unsigned char *smem, const HLayout
 template <typename T, bool CONT, bool COUNT>
 __device__ int hrow(const HProblem<T> &p, int64_t inst, unsigned char *smem, const HLayout &y,
                     int lane, int s, T tfree, uint64_t mask, int n, T inc, T rho, uint64_t *todo,
-                    int &nfeas, int64_t &nevals) {
+                    int &nfeas, int &nevals) {
   const int K = p.K, K4 = y.K4;
   const T *sC = (const T *)(smem + y.C), *sA = (const T *)(smem + y.A);
   const T *sB = (const T *)(smem + y.B), *sdl = (const T *)(smem + y.dl);
@@ -705,7 +712,7 @@ __device__ inline T offload_cpu_energy(const unsigned char *smem, const HLayout 
 template <typename T, bool COUNT, bool GREEDY, bool CONT, int LG = 0>
 __device__ void hsearch(const HProblem<T> &p, int64_t inst, unsigned char *smem, const HLayout &y,
                         int lane, uint64_t mask, int n, T tfree, T inc, T rho, T &bestE,
-                        int &bestI, int &nfeas, int64_t &nevals) {
+                        int &bestI, int &nfeas, int &nevals) {
   const int N = p.N, K = p.K, J = p.J, s_end = p.s_end, j_low = p.j_low;
   const T *sr = (const T *)(smem + y.r), *sP = (const T *)(smem + y.P);
   const Batch<T> *sbt = (const Batch<T> *)(smem + y.bt);
@@ -959,7 +966,7 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_hetero_kernel(HArgs<T> args) {
   hprepare<T, CONT>(p, inst, smem, y, lane);
   T bestE = inf_of<T>();
   int bestI = 0x7fffffff, nfeas = 0;
-  int64_t nevals = 0;
+  int nevals = 0;
   const T rho =
       gpu_energy_rate((const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, J, lane);
   T eLC;
@@ -974,13 +981,13 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_hetero_kernel(HArgs<T> args) {
     nfeas += (lane == 0) ? 1 : 0;
     if (better(eLC, idxLC, bestE, bestI)) { bestE = eLC; bestI = idxLC; }
   }
-  const int64_t totfeas = wave_sum_i64((int64_t)nfeas);
-  const int64_t totev = wave_sum_i64(nevals);
-
   const auto *a = hargs<T>();
-  if (lane == 0) {
-    if (a->out.nfeas) a->out.nfeas[inst] = (int32_t)totfeas;
-    if (a->out.nevals) a->out.nevals[inst] = totev;
+  if constexpr (COUNT) {
+    const int64_t totfeas = wave_sum_i64(nfeas), totev = wave_sum_i64(nevals);
+    if (lane == 0) {
+      if (a->out.nfeas) a->out.nfeas[inst] = (int32_t)totfeas;
+      if (a->out.nevals) a->out.nevals[inst] = totev;
+    }
   }
   UserOut<T> uo;
   uo.level = a->out.ulevel + inst * N;
@@ -1082,7 +1089,7 @@ __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> 
       gpu_energy_rate((const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, J, lane);
   // the group's winner among its candidates and local computing, with the
   // GPU free at tf0 (0x7fffffff if none is feasible); counts into nf, ne
-  auto group_search = [&](uint64_t mask, int n, T tf0, int &nf, int64_t &ne) -> int {
+  auto group_search = [&](uint64_t mask, int n, T tf0, int &nf, int &ne) -> int {
     T bestE = inf_of<T>();
     int bestI = 0x7fffffff;
     T eLC;
@@ -1098,7 +1105,8 @@ __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> 
   };
 
   int nfeas = 0;
-  int64_t nevals = 0, ninner = 0;
+  int nevals = 0;
+  int64_t ninner = 0, nfeas_all = 0, nevals_all = 0;
   const UserOut<T> none{nullptr, nullptr, nullptr, nullptr, 0};
   for (int i = 1; i <= N; ++i) {
     int ni = 0;  // states in the front of prefix i
@@ -1131,6 +1139,11 @@ __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> 
           tk = k >= 0 ? uni(fT[j * F + k]) : tk;
         } while (k >= 0 && H >= tk);
       }
+      if constexpr (COUNT) {  // (a lane's sums over one group stay below 2^31)
+        nfeas_all += wave_sum_i64(nfeas);
+        nevals_all += wave_sum_i64(nevals);
+        nfeas = nevals = 0;
+      }
     }
     if (lane == 0) fn[i] = ni;
     __syncthreads();
@@ -1151,12 +1164,12 @@ __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> 
     a->out.ugroup[o + q] = -1;
     if (a->out.ufreq) a->out.ufreq[o + q] = T(0);
   }
-  const int64_t totfeas = wave_sum_i64((int64_t)nfeas);
-  const int64_t totev = wave_sum_i64(nevals);
-  if (lane == 0) {
-    if (a->out.ninner) a->out.ninner[inst] = ninner;
-    if (a->out.nfeas) a->out.nfeas[inst] = totfeas;
-    if (a->out.nevals) a->out.nevals[inst] = totev;
+  if constexpr (COUNT) {
+    if (lane == 0) {
+      if (a->out.ninner) a->out.ninner[inst] = ninner;
+      if (a->out.nfeas) a->out.nfeas[inst] = nfeas_all;
+      if (a->out.nevals) a->out.nevals[inst] = nevals_all;
+    }
   }
   if (uni(fn[N]) == 0) {
     if (lane == 0) {
@@ -1191,7 +1204,7 @@ __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> 
     const uint64_t mask = members(start, b);
     const T tf0 = uni(fT[from[uni(eks[gno])]]);
     int nf = 0;
-    int64_t ne = 0;
+    int ne = 0;
     const int idx = group_search(mask, n, tf0, nf, ne);
     uo.gno = gno;
     T Eg, Tg;
@@ -1368,7 +1381,7 @@ int validate_hetero(const jdob_problem *p, bool grouped) {
   const int sz = p->dtype == JDOB_F64 ? 8 : 4;
   if (make_hlayout(p->num_users, p->num_layers, p->num_local_levels, p->num_gpu_levels, sz,
                    grouped)
-          .total > LDS_LIMIT)
+          .limit > LDS_LIMIT)
     return JDOB_ERR_UNSUPPORTED;
   return JDOB_OK;
 }
