@@ -30,8 +30,8 @@
 //     bounds: partition points, batches and candidates whose bound exceeds
 //     the energy of local computing or of a candidate found before can
 //     neither win nor tie (see beaten).  Searched best bound first, few are
-//     left: 1,048,576 instances of 32 users, 22 layers 9.5 -> 1.55 ms, 65,537
-//     of 128 users, 50 layers 12.5 -> 1.09 ms, the grouping of 65,536
+//     left: 1,048,576 instances of 32 users, 22 layers 9.5 -> 1.02 ms, 65,537
+//     of 128 users, 50 layers 12.7 -> 0.94 ms, the grouping of 65,536
 //     instances of 10 users 22.7 -> 4.8 ms.
 // The kernel is a VALU/LDS-bound loop of compares, selects and adds: it is
 // not a dense contraction and uses no matrix cores.
@@ -46,6 +46,7 @@ using namespace jdob_dev;
 template <typename T> struct Problem {
   const T *cyc, *bits, *alpha, *beta, *rate, *deadline, *tfree, *lf, *gf;
   T kappa, ptx, gc, p0;
+  T gopt;     // best_gpu_freq
   int N, L, K, J;
   int s_end;  // partition points searched: s in [0, s_end) (1 with binary offloading)
   int j_low;  // GPU levels searched: j in [j_low, J) (J-1 without edge DVFS)
@@ -262,6 +263,7 @@ template <typename T> __device__ inline Problem<T> own_problem(const Problem<T> 
   p.ptx = own(q.ptx);
   p.gc = own(q.gc);
   p.p0 = own(q.p0);
+  p.gopt = own(q.gopt);
   p.N = own(q.N);
   p.L = own(q.L);
   p.K = own(q.K);
@@ -1031,8 +1033,8 @@ template <typename T, bool FROM_TABLES, bool ONE_CHUNK, bool COUNT, bool GREEDY,
           bool QUEUE>
 __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &tab, int64_t inst,
                                          unsigned char *smem, const Layout &y, int lane, int N,
-                                         int blo, T tfree, T inc, T rho, T &bestE, int &bestI,
-                                         int &nfeas, int &nevals, bool flags_ready = false) {
+                                         int blo, T tfree, T inc, const GpuCost<T> &gpu,
+                                         T &bestE, int &bestI, int &nfeas, int &nevals, bool flags_ready = false) {
   const int L = p.L, K = p.K, J = p.J;
   const int s_end = p.s_end, j_low = p.j_low;
   T *sC = (T *)(smem + y.C), *sA = (T *)(smem + y.A), *sB = (T *)(smem + y.B);
@@ -1375,21 +1377,32 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
       // the least GPU energy and with every offloader at the lowest frequency
       // that the first one, whose budget is the largest, can run at.
       uint64_t todo;
+      T lb;
       {
         const int b = c0 + lane;
         const Batch<T> r = sbt[b <= N ? b : N + 1];
         const T H = r.lo - r.ab * rtop;
         const bool ok = (b <= N) & (H >= tfree) & (tK1 <= H - r.upl);
-        const T lb = fma_(T(b), least_cpu(Cs, kC, H - up0, f0), fma_(rho, r.ab, r.esl));
+        const T due = tK1 + r.upl, room = r.lo - (due > tfree ? due : tfree);
+        lb = fma_(T(b), least_cpu(Cs, kC, H - up0, f0), gpu.least(r.ab, room, r.lo) + r.esl);
         const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
         if (okm == 0) break;
+        lb = ok ? lb : inf_of<T>();
         todo = okm & ~__builtin_amdgcn_ballot_w64(beaten(lb, inc));
       }
       int next = c0 + WAVE;
       while (todo) {
-      const int b0 = c0 + __builtin_ctzll(todo);
+      int q = __builtin_ctzll(todo);
+      if (CONT && nb == 1) {  // best bound first (no level is carried from pass to pass)
+        const T m = wave_min(lb);
+        if (!(m < inf_of<T>()) || beaten(m, inc)) break;
+        q = __builtin_ctzll(__builtin_amdgcn_ballot_w64(lb == m));
+        lb = lane == q ? inf_of<T>() : lb;
+      } else {
+        todo = q + nb < WAVE ? todo & (~uint64_t(0) << (q + nb)) : 0;
+      }
+      const int b0 = c0 + q;
       next = b0 + nb > next ? b0 + nb : next;
-      todo = b0 + nb - c0 < WAVE ? todo & (~uint64_t(0) << (b0 + nb - c0)) : 0;
       for (int jc = 0; jc < (ONE_CHUNK ? WAVE : Jn); jc += WAVE) {
         const int j = j_low + jc + jl;
         const bool jok = one_chunk ? !idle : j < J;
@@ -1498,7 +1511,8 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
           }
         }
         if (one_chunk) {
-          const bool take = valid & (E <= bE);
+          // (of equal energies the larger batch, the lower flat index)
+          const bool take = valid & (CONT ? (E < bE) | ((E == bE) & (b > bI)) : E <= bE);
           bE = take ? E : bE;
           bI = take ? b : bI;
           lower_inc(take, E);
@@ -1553,8 +1567,8 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
 
   // Partition points by their lowest bound, until it is beaten by the best
   // energy found: the winner's is usually among the first (10 users in a
-  // group: 22 partition points hold feasible candidates, 1.5 are searched; 32
-  // users: 13 and 0.1; 128 users: 14 and 7).  A partition point's bound is the
+  // group: 22 partition points hold feasible candidates, 1.3 are searched; 32
+  // users: 13 and 0.1; 128 users: 14 and 6).  A partition point's bound is the
   // least over b of: the least GPU energy, the upload energy of the first b
   // users, the local energy of the others, and b users' CPU energy at the
   // lowest frequency that the first user, whose budget is the largest, can run
@@ -1598,16 +1612,18 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
       for (int b = blo + part; b <= N; b += parts) {
         const Batch<T> r = sbt[b];
         const T ab = As + Bs * T(b), H = r.lo - ab * rtop;
-        const bool ok = (H >= tfree) & (tmin <= H - Os * r.upl);
-        const T e = fma_(T(b), least_cpu(Cs, kC, H - up0, f0), fma_(rho, ab, fma_(pO, r.ab, r.esl)));
+        const T up = Os * r.upl, room = r.lo - (tmin + up > tfree ? tmin + up : tfree);
+        const bool ok = (H >= tfree) & (tmin <= H - up);
+        const T e = fma_(T(b), least_cpu(Cs, kC, H - up0, f0),
+                         gpu.least(ab, room, r.lo) + fma_(pO, r.ab, r.esl));
         lb = (ok & (e < lb)) ? e : lb;
         if constexpr (COUNT && !GREEDY) {
-          const T up = upload_time<T, FROM_TABLES>(p, tab, inst, sbits, srate, spi, sc, b - 1);
+          const T upx = upload_time<T, FROM_TABLES>(p, tab, inst, sbits, srate, spi, sc, b - 1);
           int low = 0;  // levels that miss a deadline
           for (int step = jtop; step > 0; step >>= 1) {
             const int c = low + step;
             const T Hj = r.lo - ab * sr[c <= Jn ? j_low + c - 1 : J - 1];
-            low = (c <= Jn && !(Hj >= tfree && tmin <= Hj - up)) ? c : low;
+            low = (c <= Jn && !(Hj >= tfree && tmin <= Hj - upx)) ? c : low;
           }
           if ((open >> (lane >> lg)) & 1) {
             nfeas += Jn - low;
@@ -1700,7 +1716,8 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_solve_kernel(SolveArgs<T> args) 
   if (any)
     search_candidates<T, FROM_TABLES, ONE_CHUNK, COUNT, GREEDY, CONT, QUEUE>(
         p, tab, inst, smem, y, lane, N, blo, tfree, uni(bmin) == 0 ? uni(sSL[0]) : inf_of<T>(),
-        gpu_energy_rate(sr, sP, p.j_low, J, lane), bestE, bestI, nfeas, nevals, !FROM_TABLES);
+        GpuCost<T>(p.gf, sr, sP, p.j_low, J, p.gopt, p.gc, p.p0), bestE, bestI, nfeas, nevals,
+        !FROM_TABLES);
 
   // local computing competes last
   const int idxLC = L * J * N;
@@ -2039,7 +2056,8 @@ __global__ __launch_bounds__(WAVE, 7) void jdob_grouped_kernel(GroupedArgs<T> ar
   }
   __syncthreads();
 
-  const T rho = gpu_energy_rate((const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, J, lane);
+  const GpuCost<T> gpu(p.gf, (const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, J, p.gopt,
+                       p.gc, p.p0);
   // The group's winner among its candidates and local computing: the flat
   // index (0x7fffffff if none is feasible), with the GPU free at tf0.
   // Counts into nf, ne when COUNT.
@@ -2048,7 +2066,7 @@ __global__ __launch_bounds__(WAVE, 7) void jdob_grouped_kernel(GroupedArgs<T> ar
     int bestI = 0x7fffffff;
     search_candidates<T, false, ONE_CHUNK, COUNT, GREEDY, CONT, false>(
         p, tab, inst, smem, y, lane, g, bmin > 1 ? bmin : 1, tf0,
-        bmin == 0 ? uni(sSL[0]) : inf_of<T>(), rho, bestE, bestI, nf, ne);
+        bmin == 0 ? uni(sSL[0]) : inf_of<T>(), gpu, bestE, bestI, nf, ne);
     wave_argmin(bestE, bestI);
     if (bmin == 0) {  // local computing of the whole group competes last
       if (COUNT) nf += (lane == 0) ? 1 : 0;
@@ -2631,6 +2649,7 @@ template <typename T> Problem<T> to_problem(const jdob_problem *q) {
   p.ptx = (T)q->p_tx;
   p.gc = (T)q->gpu_c;
   p.p0 = (T)q->gpu_p_static;
+  p.gopt = (T)best_gpu_freq(q->gpu_c, q->gpu_p_static);
   p.N = q->num_users;
   p.L = q->num_layers;
   p.K = q->num_local_levels;

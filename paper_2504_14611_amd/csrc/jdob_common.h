@@ -233,6 +233,23 @@ __device__ inline T wave_scan(T v, int) {
   return wave_iscan(v, T(0), [](T a, T b) { return a + b; });
 }
 
+// Wave-uniform copies of values the compiler cannot prove uniform.
+__device__ inline int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ inline float uni(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+__device__ inline double uni(double v) {
+  const long long q = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readfirstlane((int)(q & 0xffffffff));
+  const int hi = __builtin_amdgcn_readfirstlane((int)(q >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Fused multiply-add for energies that only rank candidates (every decision
+// uses separately rounded operations).
+__device__ inline float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // Energy bounds.  A candidate's ranking energy is a sum of non-negative terms,
 // so a sum with every term replaced by a lower bound of it cannot exceed it by
 // more than rounding: at most about 2 N roundings of 2^-24 (binary32, N <=
@@ -279,6 +296,50 @@ __device__ inline T gpu_energy_rate(const T *sr, const T *sP, int j_low, int J, 
   return wave_min(v);
 }
 
+// The GPU energy of a batch from below.  With ab its latency at the top level
+// and r = gtop / g the stretch it is ab * (c3 / r^2 + p0 * r), c3 = gc * gtop^3
+// (Eq. (5)): falling in r up to the stretch of g_opt = cbrt(p0 / (2 gc)),
+// rising from there.  A batch that must be done in `room` needs r <= room / ab,
+// where the second term is p0 * room.  So the least is there, or at g_opt (not
+// below the lowest level searched) if that is faster.  room is a difference of
+// times up to lo: a little is added for its rounding.  Up to four levels, which
+// may lie far apart, are tried one by one instead (two levels a factor of ten
+// apart, 347 instances of 7 users, 50 layers: 199 us without, 76 us).
+template <typename T> struct GpuCost {
+  T c3, p0, qmin, cost;  // qmin: 1 / stretch of g_opt; cost: energy per second of ab there
+  const T *r, *P;        // stretch and power of the levels searched
+  int n;                 // their number
+  __device__ inline GpuCost(const T *gf, const T *sr, const T *sP, int j_low, int J, T gopt, T gc,
+                            T s) {
+    const T gtop = gf[J - 1], lo = gf[j_low], m = gopt > lo ? gopt : lo;
+    const T g = m < gtop ? m : gtop;
+    c3 = uni(gc * gtop * gtop * gtop);
+    p0 = s;
+    qmin = uni(g * rough_rcp(gtop));
+    cost = uni(fma_(c3 * qmin, qmin, p0 * rough_rcp(qmin)));
+    r = sr + j_low;
+    P = sP + j_low;
+    n = J - j_low;
+  }
+  __device__ inline T least(T ab, T room, T lo) const {
+    const T some = fma_(lo, T(0x1p-20), room);
+    if (n <= 4) {
+      T v = inf_of<T>();
+      for (int j = 0; j < n; ++j) {
+        const T e = P[j] * r[j];
+        v = (ab * r[j] <= some) & (e < v) ? e : v;
+      }
+      return v < inf_of<T>() ? ab * v : T(0);  // (no level: infeasible)
+    }
+    // (where room <= 0 makes q negative or NaN, nothing is feasible)
+    const T q = ab * rough_rcp(some);
+    return q > qmin ? fma_(c3 * ab, q * q, p0 * room) : ab * cost;
+  }
+};
+
+// The frequency at which a second of top-level batch latency costs least.
+inline double best_gpu_freq(double gc, double p0) { return gc > 0 ? cbrt(p0 / (2.0 * gc)) : INFINITY; }
+
 // A copy of a uniform value in scalar registers of its own.  Kernel arguments
 // arrive in wide loads (eight or sixteen registers at a time); without the
 // copy, a spill under register pressure saves and restores the whole group.
@@ -301,17 +362,6 @@ __device__ inline double from_upper_half(double v) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// Wave-uniform copies of values the compiler cannot prove uniform.
-__device__ inline int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ inline float uni(float v) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
-}
-__device__ inline double uni(double v) {
-  const long long q = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readfirstlane((int)(q & 0xffffffff));
-  const int hi = __builtin_amdgcn_readfirstlane((int)(q >> 32));
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
 // Inclusive wavefront prefix sum with DPP row shifts and row broadcasts (the
 // summation order differs from a sequential sum: used for energies that only
 // rank candidates).
@@ -345,10 +395,6 @@ __device__ inline double scan_add(double v) {
   return v;
 }
 
-// Fused multiply-add for energies that only rank candidates (every decision
-// uses separately rounded operations).
-__device__ inline float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ inline double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 __device__ inline int64_t instance_of_block(int64_t first) {
   // Consecutive workgroups are dealt round-robin to the 8 XCDs; give each XCD

@@ -44,6 +44,7 @@ template <typename T> struct HProblem {
   const T *cyc, *bits, *alpha, *beta, *rate, *deadline, *tfree, *lf, *gf;
   const T *uzeta, *ukappa, *uptx, *ulf;  // per user, or nullptr: the shared value
   T kappa, ptx, gc, p0;
+  T gopt;  // best_gpu_freq
   int N, L, K, J;
   int s_end, j_low;
 };
@@ -420,12 +421,12 @@ __device__ inline int feasible_levels(const HProblem<T> &p, const T *sr, T lo, T
 // energy of each offloader at the lowest frequency at which it could close a
 // batch of its own, which no larger batch lets it go below; feasibility
 // falls with b and rises with j, so the test is that of the top GPU level.
-// (16 users, 22 layers: 6.5 of 21.5 partition points with feasible candidates
-// are then searched, best bound first; 17 of the batches of 72 passes.)
+// (16 users, 22 layers: 5.5 of 21.5 partition points with feasible candidates
+// are then searched, best bound first; 13 of the batches of 72 passes.)
 // Counts the feasible candidates into nfeas, nevals when COUNT.
 template <typename T, bool COUNT>
 __device__ void hbounds(const HProblem<T> &p, unsigned char *smem, const HLayout &y, int lane,
-                        uint64_t mask, T tfree, T rho, T *slb, int &nfeas, int &nevals) {
+                        uint64_t mask, T tfree, const GpuCost<T> &gpu, T *slb, int &nfeas, int &nevals) {
   const int N = p.N, K = p.K, J = p.J;
   const T *sC = (const T *)(smem + y.C), *sA = (const T *)(smem + y.A);
   const T *sB = (const T *)(smem + y.B), *sr = (const T *)(smem + y.r);
@@ -484,7 +485,8 @@ __device__ void hbounds(const HProblem<T> &p, unsigned char *smem, const HLayout
       nfeas += ok ? c : 0;
       nevals += ok ? c * b : 0;
     }
-    const T lb = run_reduce(ok ? fma_(rho, ab, off + sl) : inf_of<T>(), lg,
+    const T room = lo - (nd > tfree ? nd : tfree);
+    const T lb = run_reduce(ok ? gpu.least(ab, room, lo) + (off + sl) : inf_of<T>(), lg,
                             [](T a, T b) { return b < a ? b : a; });
     if (q == 0 && s0 + r < p.s_end) slb[s0 + r] = lb;
     __syncthreads();
@@ -500,8 +502,8 @@ __device__ void hbounds(const HProblem<T> &p, unsigned char *smem, const HLayout
 // wave-uniform); counts the feasible candidates as hbounds does when COUNT.
 template <typename T, bool CONT, bool COUNT>
 __device__ int hrow(const HProblem<T> &p, int64_t inst, unsigned char *smem, const HLayout &y,
-                    int lane, int s, T tfree, uint64_t mask, int n, T inc, T rho, uint64_t *todo,
-                    int &nfeas, int &nevals) {
+                    int lane, int s, T tfree, uint64_t mask, int n, T inc,
+                    const GpuCost<T> &gpu, T *rb, uint64_t *todo, int &nfeas, int &nevals) {
   const int K = p.K, K4 = y.K4;
   const T *sC = (const T *)(smem + y.C), *sA = (const T *)(smem + y.A);
   const T *sB = (const T *)(smem + y.B), *sdl = (const T *)(smem + y.dl);
@@ -557,7 +559,9 @@ __device__ int hrow(const HProblem<T> &p, int64_t inst, unsigned char *smem, con
   const T esl = eu + slnext;
   const T cl =
       run_iscan(in ? least_cpu(us.z, skc[lane], Htop - us.up, us.fmin) : T(0), T(0), lg, add);
-  *todo = ok & ~__builtin_amdgcn_ballot_w64(beaten(fma_(rho, ab, esl + cl), inc));
+  const T lb = gpu.least(ab, lo - (nd > tfree ? nd : tfree), lo) + (esl + cl);
+  *rb = (ok >> lane) & 1 ? lb : inf_of<T>();
+  *todo = ok & ~__builtin_amdgcn_ballot_w64(beaten(lb, inc));
   if (!*todo) return bmin;
   if (in) {
     Batch<T> r;
@@ -711,8 +715,8 @@ __device__ inline T offload_cpu_energy(const unsigned char *smem, const HLayout 
 // nevals when COUNT.
 template <typename T, bool COUNT, bool GREEDY, bool CONT, int LG = 0>
 __device__ void hsearch(const HProblem<T> &p, int64_t inst, unsigned char *smem, const HLayout &y,
-                        int lane, uint64_t mask, int n, T tfree, T inc, T rho, T &bestE,
-                        int &bestI, int &nfeas, int &nevals) {
+                        int lane, uint64_t mask, int n, T tfree, T inc,
+                        const GpuCost<T> &gpu, T &bestE, int &bestI, int &nfeas, int &nevals) {
   const int N = p.N, K = p.K, J = p.J, s_end = p.s_end, j_low = p.j_low;
   const T *sr = (const T *)(smem + y.r), *sP = (const T *)(smem + y.P);
   const Batch<T> *sbt = (const Batch<T> *)(smem + y.bt);
@@ -736,8 +740,9 @@ __device__ void hsearch(const HProblem<T> &p, int64_t inst, unsigned char *smem,
   auto search_point = [&](auto by_bounds, int s) {
     constexpr bool bounds = decltype(by_bounds)::value;
     uint64_t todo;
+    T rb;  // the bound of batch size lane + 1
     const int bmin = hrow<T, CONT, COUNT && !GREEDY && !bounds>(
-        p, inst, smem, y, lane, s, tfree, mask, n, inc, rho, &todo, nfeas, nevals);
+        p, inst, smem, y, lane, s, tfree, mask, n, inc, gpu, &rb, &todo, nfeas, nevals);
     const int blo = bmin > 1 ? bmin : 1;
     if (!todo) return;
     const int sJN = s * J * n;
@@ -780,9 +785,18 @@ __device__ void hsearch(const HProblem<T> &p, int64_t inst, unsigned char *smem,
         lower_inc(take, E);
       }
     } else {
+      // one batch size a pass: best bound first; several: in order
       while (todo) {
-        const int b0 = 1 + __builtin_ctzll(todo);
-        todo = b0 - 1 + nb < WAVE ? todo & (~uint64_t(0) << (b0 - 1 + nb)) : 0;
+        int q = __builtin_ctzll(todo);
+        if (nb == 1) {
+          const T least = wave_min(rb);
+          if (!(least < inf_of<T>()) || beaten(least, inc)) break;
+          q = __builtin_ctzll(__builtin_amdgcn_ballot_w64(rb == least));
+          rb = lane == q ? inf_of<T>() : rb;
+        } else {
+          todo = q + nb < WAVE ? todo & (~uint64_t(0) << (q + nb)) : 0;
+        }
+        const int b0 = q + 1;
         for (int jc = 0; jc < Jn; jc += WAVE) {
           const int j = j_low + jc + jl;
           const bool jok = !idle && j < J;
@@ -823,7 +837,7 @@ __device__ void hsearch(const HProblem<T> &p, int64_t inst, unsigned char *smem,
     return;
   }
   T *slb = (T *)(smem + y.cyc);  // (the layers' cycles have been summed)
-  hbounds<T, COUNT && !GREEDY>(p, smem, y, lane, mask, tfree, rho, slb, nfeas, nevals);
+  hbounds<T, COUNT && !GREEDY>(p, smem, y, lane, mask, tfree, gpu, slb, nfeas, nevals);
   for (int s0 = 0; s0 < s_end; s0 += WAVE) {
     T lb = s0 + lane < s_end ? slb[s0 + lane] : inf_of<T>();
     while (true) {
@@ -967,12 +981,12 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_hetero_kernel(HArgs<T> args) {
   T bestE = inf_of<T>();
   int bestI = 0x7fffffff, nfeas = 0;
   int nevals = 0;
-  const T rho =
-      gpu_energy_rate((const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, J, lane);
+  const GpuCost<T> gpu(p.gf, (const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, J, p.gopt,
+                       p.gc, p.p0);
   T eLC;
   const bool local = hlocal<T>(smem, y, lane, all, N, &eLC);
   hsearch<T, COUNT, GREEDY, CONT, LG>(
-      p, inst, smem, y, lane, all, N, tfree, local ? eLC : inf_of<T>(), rho, bestE, bestI, nfeas,
+      p, inst, smem, y, lane, all, N, tfree, local ? eLC : inf_of<T>(), gpu, bestE, bestI, nfeas,
       nevals);
   // local computing competes last
   const int idxLC = L * J * N;
@@ -1036,9 +1050,9 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_hetero_kernel(HArgs<T> args) {
 // dynamic program keeps, per prefix of the deadline order, the front of
 // non-dominated (total energy, GPU release time) states, as the other
 // grouping kernel does.  Six waves per SIMD: at more, values spill
-// to scratch (16,384 x 10 users, continuous: 5.19 ms at six waves, 5.43 at
-// seven, 5.75 at eight, 5.56 at five; 9.3 before the bounds and the orders
-// kept per partition point).
+// to scratch (16,384 x 10 users, continuous, before the bound of the GPU energy
+// knew the batch's time: 5.19 ms at six waves, 5.43 at seven, 5.75 at eight,
+// 5.56 at five; 3.25 ms now, 9.3 before the bounds).
 template <typename T, bool COUNT, bool GREEDY, bool CONT>
 __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> args) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1085,8 +1099,8 @@ __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> 
     const int r = dr[lane < N ? lane : 0];
     return __builtin_amdgcn_ballot_w64(lane < N && r >= lo && r < hi);
   };
-  const T rho =
-      gpu_energy_rate((const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, J, lane);
+  const GpuCost<T> gpu(p.gf, (const T *)(smem + y.r), (const T *)(smem + y.P), p.j_low, J, p.gopt,
+                       p.gc, p.p0);
   // the group's winner among its candidates and local computing, with the
   // GPU free at tf0 (0x7fffffff if none is feasible); counts into nf, ne
   auto group_search = [&](uint64_t mask, int n, T tf0, int &nf, int &ne) -> int {
@@ -1095,7 +1109,7 @@ __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> 
     T eLC;
     const bool local = hlocal<T>(smem, y, lane, mask, N, &eLC);
     hsearch<T, COUNT, GREEDY, CONT>(p, inst, smem, y, lane, mask, n, tf0,
-                                    local ? eLC : inf_of<T>(), rho, bestE, bestI, nf, ne);
+                                    local ? eLC : inf_of<T>(), gpu, bestE, bestI, nf, ne);
     wave_argmin(bestE, bestI);
     if (local) {
       if (COUNT) nf += (lane == 0) ? 1 : 0;
@@ -1253,6 +1267,7 @@ template <typename T> HProblem<T> to_hproblem(const jdob_problem *q) {
   p.ptx = (T)q->p_tx;
   p.gc = (T)q->gpu_c;
   p.p0 = (T)q->gpu_p_static;
+  p.gopt = (T)best_gpu_freq(q->gpu_c, q->gpu_p_static);
   p.N = q->num_users;
   p.L = q->num_layers;
   p.K = q->num_local_levels;
