@@ -492,33 +492,44 @@ __device__ inline int lanes_per_item(int n) {
 
 // The rate order pi, the batch deadlines lo[b] (Eq. (10)), the rates in pi
 // order and the local-energy suffix sums SL (ranking only) that the search
-// reads.
-template <typename T>
-__device__ inline void order_users(const Problem<T> &p, unsigned char *smem, const Layout &y,
-                                   int lane) {
+// reads; pi and lo from the stage-1 tables with FROM_TABLES (whose upload
+// times stand in for the rates).
+template <typename T, bool FROM_TABLES>
+__device__ inline void order_users(const Problem<T> &p, const Tables<T> &tab, int64_t inst,
+                                   unsigned char *smem, const Layout &y, int lane) {
   const int N = p.N;
   int16_t *spi = (int16_t *)(smem + y.pi);
   T *srate = (T *)(smem + y.rate), *slo = (T *)(smem + y.lo), *sup = (T *)(smem + y.up);
   const T *sdl = (const T *)(smem + y.dl), *seL = (const T *)(smem + y.eL);
   T *sSL = (T *)(smem + y.SL);
-  for (int i = lane; i < N; i += WAVE) spi[i] = i;  // stays a permutation of valid users
-  __syncthreads();
-  rank_users(srate, (uint64_t *)(smem + y.bt), spi, N, lane);
-  __syncthreads();
-  {
-    T carry = inf_of<T>();
-    for (int i0 = 0; i0 < N; i0 += WAVE) {
-      const int i = i0 + lane;
-      if (i < N) sup[i] = srate[spi[i]];
-      const T d = (i < N) ? sdl[spi[i]] : inf_of<T>();
-      T v = wave_scan<T, true>(d, lane);
-      v = (carry < v) ? carry : v;
-      if (i < N) slo[i + 1] = v;
-      carry = lane_read(v, WAVE - 1);
+  if constexpr (FROM_TABLES) {
+    for (int i = lane; i < N; i += WAVE) {
+      const int m = tab.order[inst * N + i];
+      spi[i] = (m >= 0 && m < N) ? m : 0;
+      slo[i + 1] = tab.lo[inst * N + i];
     }
     if (lane == 0) slo[0] = inf_of<T>();
     __syncthreads();
-    for (int i = lane; i < N; i += WAVE) srate[i] = sup[i];
+  } else {
+    for (int i = lane; i < N; i += WAVE) spi[i] = i;  // stays a permutation of valid users
+    __syncthreads();
+    rank_users(srate, (uint64_t *)(smem + y.bt), spi, N, lane);
+    __syncthreads();
+    {
+      T carry = inf_of<T>();
+      for (int i0 = 0; i0 < N; i0 += WAVE) {
+        const int i = i0 + lane;
+        if (i < N) sup[i] = srate[spi[i]];
+        const T d = (i < N) ? sdl[spi[i]] : inf_of<T>();
+        T v = wave_scan<T, true>(d, lane);
+        v = (carry < v) ? carry : v;
+        if (i < N) slo[i + 1] = v;
+        carry = lane_read(v, WAVE - 1);
+      }
+      if (lane == 0) slo[0] = inf_of<T>();
+      __syncthreads();
+      for (int i = lane; i < N; i += WAVE) srate[i] = sup[i];
+    }
   }
   {
     T carry = T(0);
@@ -559,16 +570,21 @@ __device__ inline bool beaten_by_local(T C, T A, T B, T eps0, T rho, T lc, const
   return beaten(fma_(rho, A, acc), lc);
 }
 
+template <typename T> __device__ inline bool one_per_lane(const Problem<T> &p) {
+  return p.N <= WAVE && p.L < WAVE && p.K <= WAVE && p.J <= WAVE;
+}
+
 // The preparation for up to 64 users, GPU levels and CPU levels and fewer than
-// 64 layers, one per lane: the rows are loaded together and kept in registers,
-// the sums run along the lanes, and with local computing feasible the
-// partition points that cannot beat it drop out before anything else is
-// computed.  (1,048,576 instances of 32 users, 22 layers, most of which end
-// there: 1.57 -> 1.02 ms; 200,003 of them, greedy, 298 -> 202 us; 4,096 of 8
+// 64 layers (one_per_lane), of the fused or the joint call: the rows are loaded
+// together and kept in registers, the sums run along the lanes, and with local
+// computing feasible the partition points that cannot beat it drop out before
+// anything else is computed.  (1,048,576 instances of 32 users, 22 layers, most of which end
+// there: 1.57 -> 1.02 ms; 65,536 by the joint call 155 -> 100 us; 200,003 of them, greedy, 298 -> 202 us; 4,096 of 8
 // users, 16 layers, where one wave's latency is the time, 22.3 -> 19.5 us.)
-template <typename T, bool CONT, bool KEEP>
-__device__ bool prepare_lanes(const Problem<T> &p, int64_t inst, unsigned char *smem,
-                              const Layout &y, int lane, T tfree, int &bmin_out) {
+template <typename T, bool FROM_TABLES, bool CONT, bool KEEP>
+__device__ bool prepare_lanes(const Problem<T> &p, const Tables<T> &tab, int64_t inst,
+                              unsigned char *smem, const Layout &y, int lane, T tfree,
+                              int &bmin_out) {
   const int N = p.N, L = p.L, K = p.K, J = p.J;
   T *sC = (T *)(smem + y.C), *sA = (T *)(smem + y.A), *sB = (T *)(smem + y.B);
   T *sf = (T *)(smem + y.f), *seps = (T *)(smem + y.eps);
@@ -587,8 +603,19 @@ __device__ bool prepare_lanes(const Problem<T> &p, int64_t inst, unsigned char *
   const T f = p.lf[lane < K ? lane : K - 1], g = p.gf[lane < J ? lane : J - 1];
   const T xc = p.cyc[inst * L + lc_], xa = p.alpha[inst * L + (L - 1 - lc_)];
   const T xb = p.beta[inst * L + (L - 1 - lc_)];
-  const T rate = p.rate[inst * N + mc], Tm = p.deadline[inst * N + mc];
-  const T bits = p.bits[inst * (L + 1) + (lane <= L ? lane : L)];
+  T rate = T(0), Tm = T(0), bits = T(0), ownE = T(0);
+  int own = -1, bm = 0;  // from the tables: the local level and energy, bmin
+  if constexpr (FROM_TABLES) {
+    const int64_t o = (inst * (L + 1) + L) * N + mc;
+    own = tab.slevel[o];
+    ownE = tab.senergy[o];
+    bm = tab.bmin[inst];
+    if (CONT) Tm = p.deadline[inst * N + mc];
+  } else {
+    rate = p.rate[inst * N + mc];
+    Tm = p.deadline[inst * N + mc];
+    bits = p.bits[inst * (L + 1) + (lane <= L ? lane : L)];
+  }
   const T f0 = lane_read(f, 0), ftop = lane_read(f, K - 1), gtop = lane_read(g, J - 1);
   // the sums C, A, B in the sequential order of the contract (lane i of the
   // second and third holds layer L - i on)
@@ -608,21 +635,31 @@ __device__ bool prepare_lanes(const Problem<T> &p, int64_t inst, unsigned char *
   // its deadline (latency falls with the level: binary search for the
   // number of levels that are too slow)
   const T CL = lane_read(c, L - 1), eps = p.kappa * (f * f);
-  const T tL = CL / f;
-  if (lane < K) {
-    ste[lane].t = tL;
-    ste[lane].e = eps * CL;
-    sf[lane] = f;
+  if (lane < K) sf[lane] = f;
+  int kL;
+  T eL;
+  bool has;
+  if constexpr (FROM_TABLES) {
+    has = own >= 0 && own < K;
+    kL = has ? own : -1;
+    eL = has ? ownE : inf_of<T>();
+    bm = bm < 0 ? 0 : (bm > N ? N + 1 : bm);
+  } else {
+    const T tL = CL / f;
+    if (lane < K) {
+      ste[lane].t = tL;
+      ste[lane].e = eps * CL;
+    }
+    __syncthreads();
+    int kc = 0;
+    for (int step = K > 1 ? 1 << (31 - __clz(K - 1)) : 0; step > 0; step >>= 1) {
+      const int nc = kc + step;
+      kc = (nc <= K && ste[nc <= K ? nc - 1 : 0].t > Tm) ? nc : kc;
+    }
+    has = kc < K && ste[kc < K ? kc : 0].t <= Tm;
+    kL = has ? kc : -1;
+    eL = has ? ste[kc < K ? kc : 0].e : inf_of<T>();
   }
-  __syncthreads();
-  int kc = 0;
-  for (int step = K > 1 ? 1 << (31 - __clz(K - 1)) : 0; step > 0; step >>= 1) {
-    const int nc = kc + step;
-    kc = (nc <= K && ste[nc <= K ? nc - 1 : 0].t > Tm) ? nc : kc;
-  }
-  const bool has = kc < K && ste[kc < K ? kc : 0].t <= Tm;
-  const int kL = has ? kc : -1;
-  T eL = has ? ste[kc < K ? kc : 0].e : inf_of<T>();
   if (CONT) {  // Eq. (20) with its clamp against the user's deadline
     T fL = T(0);
     if (has) {
@@ -635,7 +672,7 @@ __device__ bool prepare_lanes(const Problem<T> &p, int64_t inst, unsigned char *
     skL[lane] = (int8_t)kL;
     seL[lane] = eL;
   }
-  const uint64_t bad = __builtin_amdgcn_ballot_w64(ism && !has);
+  const uint64_t bad = FROM_TABLES ? (uint64_t)(bm != 0) : __builtin_amdgcn_ballot_w64(ism && !has);
   // GPU power at level `lane`, and the stretch of its latency
   const T P = p.gc * ((g * g) * g) + p.p0;
 
@@ -661,51 +698,63 @@ __device__ bool prepare_lanes(const Problem<T> &p, int64_t inst, unsigned char *
       return false;
     }
     if (lg > 0) {  // gather every 2^lg-th bit: lane s asks for bit s << lg
-      cand = __builtin_amdgcn_ballot_w64(lane < (WAVE >> lg) && ((keep >> ((lane << lg) & 63)) & 1));
+      cand = __builtin_amdgcn_ballot_w64(lane < (WAVE >> lg) &&
+                                         ((keep >> ((lane << lg) & 63)) & 1));
     } else {
       cand = keep;
     }
     __syncthreads();
   }
 
-  // 3. bmin and the blo-th user of pi without sorting (pi orders users by rate
-  // descending, ties by lower index).  The last user of pi without a local
-  // level has the lowest rate among them, then the highest index.
-  int bmin = 0, ub;
-  T rb, lob;
-  if (bad) {
-    const bool mine = ism && !has;
-    rb = wave_min(mine ? rate : inf_of<T>());
-    const uint64_t at = __builtin_amdgcn_ballot_w64(mine && rate == rb);
-    ub = at ? 63 - __clzll((long long)at) : 0;  // (none only with rates outside the contract)
-    const bool ahead = ism && (rate > rb || (rate == rb && lane <= ub));
-    bmin = __popcll(__builtin_amdgcn_ballot_w64(ahead));
-    lob = wave_min(ahead ? Tm : inf_of<T>());
+  if constexpr (FROM_TABLES) {  // (no test without the users' upload times)
+    bmin_out = bm;
+    if (lane < p.s_end) sflag[lane] = (cand >> lane) & 1;
   } else {
-    rb = wave_max(ism ? rate : -inf_of<T>());
-    const uint64_t at = __builtin_amdgcn_ballot_w64(ism && rate == rb);
-    ub = at ? __builtin_ctzll(at) : 0;
-    lob = lane_read(Tm, ub);
-  }
-  bmin_out = bmin;
-  const int blo = bmin > 1 ? bmin : 1;
-
-  // 4. the test of every partition point left at the top GPU level (where the
-  // stretch is 1) and blo
-  const int s = lane < p.s_end ? lane : 0;
-  const T tK1 = lane_before(c) / ftop;  // C[s] over the top CPU level
-  const T upl = bits / rb;
-  const T Phi = sA[s] + sB[s] * T(blo);
-  const T H = lob - Phi;
-  const bool ok = lane < p.s_end && ((cand >> lane) & 1) && (H >= tfree) && (tK1 <= H - upl);
-  if (lane < p.s_end) sflag[lane] = ok;
-  if (!__builtin_amdgcn_ballot_w64(ok)) {
-    if (bmin == 0) {  // local computing is the only candidate: its ranking energy
-      const T lc = lane_read(run_reduce(ism ? eL : T(0), 6, add), 0);
-      if (lane == 0) sSL[0] = lc;
+    // 3. bmin and the blo-th user of pi without sorting (pi orders users by rate
+    // descending, ties by lower index).  The last user of pi without a local
+    // level has the lowest rate among them, then the highest index.
+    int bmin = 0, ub;
+    T rb, lob;
+    if (bad) {
+      const bool mine = ism && !has;
+      rb = wave_min(mine ? rate : inf_of<T>());
+      const uint64_t at = __builtin_amdgcn_ballot_w64(mine && rate == rb);
+      ub = at ? 63 - __clzll((long long)at) : 0;  // (none only with rates outside the contract)
+      const bool ahead = ism && (rate > rb || (rate == rb && lane <= ub));
+      bmin = __popcll(__builtin_amdgcn_ballot_w64(ahead));
+      lob = wave_min(ahead ? Tm : inf_of<T>());
+    } else {
+      rb = wave_max(ism ? rate : -inf_of<T>());
+      const uint64_t at = __builtin_amdgcn_ballot_w64(ism && rate == rb);
+      ub = at ? __builtin_ctzll(at) : 0;
+      lob = lane_read(Tm, ub);
     }
-    __syncthreads();
-    return false;
+    bmin_out = bmin;
+    const int blo = bmin > 1 ? bmin : 1;
+
+    // 4. the test of every partition point left at the top GPU level (where the
+    // stretch is 1) and blo
+    const int s = lane < p.s_end ? lane : 0;
+    const T tK1 = lane_before(c) / ftop;  // C[s] over the top CPU level
+    const T upl = bits / rb;
+    const T Phi = sA[s] + sB[s] * T(blo);
+    const T H = lob - Phi;
+    const bool ok = lane < p.s_end && ((cand >> lane) & 1) && (H >= tfree) && (tK1 <= H - upl);
+    if (lane < p.s_end) sflag[lane] = ok;
+    if (!__builtin_amdgcn_ballot_w64(ok)) {
+      if (bmin == 0) {  // local computing is the only candidate: its ranking energy
+        const T lc = lane_read(run_reduce(ism ? eL : T(0), 6, add), 0);
+        if (lane == 0) sSL[0] = lc;
+      }
+      __syncthreads();
+      return false;
+    }
+
+    if (lane <= L) sbits[lane] = bits;
+    if (ism) {
+      srate[lane] = rate;
+      sdl[lane] = Tm;
+    }
   }
 
   // 5. what the search reads
@@ -714,13 +763,8 @@ __device__ bool prepare_lanes(const Problem<T> &p, int64_t inst, unsigned char *
     sr[lane] = gtop / g;
     sP[lane] = P;
   }
-  if (lane <= L) sbits[lane] = bits;
-  if (ism) {
-    srate[lane] = rate;
-    sdl[lane] = Tm;
-  }
   __syncthreads();
-  order_users(p, smem, y, lane);
+  order_users<T, FROM_TABLES>(p, tab, inst, smem, y, lane);
   return true;
 }
 
@@ -747,8 +791,9 @@ template <typename T, bool CONT, bool KEEP>
 __device__ bool prepare_fused(const Problem<T> &p, int64_t inst, unsigned char *smem,
                               const Layout &y, int lane, T tfree, int &bmin_out) {
   const int N = p.N, L = p.L, K = p.K, J = p.J;
-  if (N <= WAVE && L < WAVE && K <= WAVE && J <= WAVE)
-    return prepare_lanes<T, CONT, KEEP>(p, inst, smem, y, lane, tfree, bmin_out);
+  if (one_per_lane(p))
+    return prepare_lanes<T, false, CONT, KEEP>(p, Tables<T>{}, inst, smem, y, lane, tfree,
+                                               bmin_out);
   T *sC = (T *)(smem + y.C), *sA = (T *)(smem + y.A), *sB = (T *)(smem + y.B);
   T *sf = (T *)(smem + y.f), *seps = (T *)(smem + y.eps);
   T *sr = (T *)(smem + y.r), *sP = (T *)(smem + y.P);
@@ -930,7 +975,7 @@ __device__ bool prepare_fused(const Problem<T> &p, int64_t inst, unsigned char *
     return false;
   }
 
-  order_users(p, smem, y, lane);
+  order_users<T, false>(p, Tables<T>{}, inst, smem, y, lane);
   return true;
 }
 
@@ -1034,7 +1079,8 @@ template <typename T, bool FROM_TABLES, bool ONE_CHUNK, bool COUNT, bool GREEDY,
 __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &tab, int64_t inst,
                                          unsigned char *smem, const Layout &y, int lane, int N,
                                          int blo, T tfree, T inc, const GpuCost<T> &gpu,
-                                         T &bestE, int &bestI, int &nfeas, int &nevals, bool flags_ready = false) {
+                                         T &bestE, int &bestI, int &nfeas, int &nevals,
+                                         bool flags_ready = false) {
   const int L = p.L, K = p.K, J = p.J;
   const int s_end = p.s_end, j_low = p.j_low;
   T *sC = (T *)(smem + y.C), *sA = (T *)(smem + y.A), *sB = (T *)(smem + y.B);
@@ -1392,138 +1438,138 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
       }
       int next = c0 + WAVE;
       while (todo) {
-      int q = __builtin_ctzll(todo);
-      if (CONT && nb == 1) {  // best bound first (no level is carried from pass to pass)
-        const T m = wave_min(lb);
-        if (!(m < inf_of<T>()) || beaten(m, inc)) break;
-        q = __builtin_ctzll(__builtin_amdgcn_ballot_w64(lb == m));
-        lb = lane == q ? inf_of<T>() : lb;
-      } else {
-        todo = q + nb < WAVE ? todo & (~uint64_t(0) << (q + nb)) : 0;
-      }
-      const int b0 = c0 + q;
-      next = b0 + nb > next ? b0 + nb : next;
-      for (int jc = 0; jc < (ONE_CHUNK ? WAVE : Jn); jc += WAVE) {
-        const int j = j_low + jc + jl;
-        const bool jok = one_chunk ? !idle : j < J;
-        const T rj = one_chunk ? rj1 : sr[jok ? j : 0];
-        const Batch<T> r = sbt[b0 + bo];
-        const T Phi = r.ab * rj;                              // Eq. (5), layers s+1..L
-        const T H = r.lo - Phi;                               // slack to the batch deadline
-        const T hl = H - r.upl;                               // budget of the last offloader
-        const bool c6 = H >= tfree, c7 = tK1 <= hl;
-        const bool feas = jok & c6 & c7;                      // (6), (7); (8): b >= bmin
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(c6) & __builtin_amdgcn_ballot_w64(c7) &
-                              (one_chunk ? jokm : __builtin_amdgcn_ballot_w64(jok));
-        if (mask == 0) continue;
-        const int b = b0 + bo;
-        const T bar = inc < bE ? inc : bE;  // an energy to beat
-        T E;
-        bool valid = feas;   // E is the candidate's energy
-        if constexpr (CONT) {
-          // with every offloader at the first one's frequency, the lowest
-          const T pj = one_chunk ? pj1 : sP[jok ? j : 0];
-          const T lb = fma_(pj, Phi, fma_(T(b), least_cpu(Cs, kC, H - up0, f0), r.esl));
-          const uint64_t need = mask & ~__builtin_amdgcn_ballot_w64(beaten(lb, bar));
-          if (need == 0) continue;
-          valid = feas & !beaten(lb, bar);
-          const int hi = 63 - __clzll((long long)need);
-          const int bpass = b0 + __builtin_amdgcn_readlane(bo, hi);  // largest b needed
-          const T Hu = feas ? H : inf_of<T>();
-          const T f2 = (Cs > T(0)) ? cont_sum_f2(sup, Hu, b, b0, bpass, Cs, fmin, fmax) : T(0);
-          E = fma_(pj, Phi, fma_(kC, f2, r.esl));
+        int q = __builtin_ctzll(todo);
+        if (CONT && nb == 1) {  // best bound first (no level is carried from pass to pass)
+          const T m = wave_min(lb);
+          if (!(m < inf_of<T>()) || beaten(m, inc)) break;
+          q = __builtin_ctzll(__builtin_amdgcn_ballot_w64(lb == m));
+          lb = lane == q ? inf_of<T>() : lb;
         } else {
-          // Eq. (20) for the first offloader: the number of levels too slow
-          // for its budget (latency falls with the level), by steps up from
-          // the level of the lane's previous pass with one chunk (a binary
-          // search on the first pass measured slower), else by binary search
-          // (an infeasible lane's budget is +inf: level 0, no steps)
-          const T x0 = (feas ? H : inf_of<T>()) - up0;
-          if (!one_chunk) {
-            const Level<T> *c0 = ste - 1;  // one before the first level that fits
-            for (int step = K2 >> 1; step > 0; step >>= 1)
-              c0 += (c0[step].t > x0) ? step : 0;
-            p0 = c0 + 1;
-            q0 = *p0;
+          todo = q + nb < WAVE ? todo & (~uint64_t(0) << (q + nb)) : 0;
+        }
+        const int b0 = c0 + q;
+        next = b0 + nb > next ? b0 + nb : next;
+        for (int jc = 0; jc < (ONE_CHUNK ? WAVE : Jn); jc += WAVE) {
+          const int j = j_low + jc + jl;
+          const bool jok = one_chunk ? !idle : j < J;
+          const T rj = one_chunk ? rj1 : sr[jok ? j : 0];
+          const Batch<T> r = sbt[b0 + bo];
+          const T Phi = r.ab * rj;                              // Eq. (5), layers s+1..L
+          const T H = r.lo - Phi;                               // slack to the batch deadline
+          const T hl = H - r.upl;                               // budget of the last offloader
+          const bool c6 = H >= tfree, c7 = tK1 <= hl;
+          const bool feas = jok & c6 & c7;                      // (6), (7); (8): b >= bmin
+          const uint64_t mask = __builtin_amdgcn_ballot_w64(c6) & __builtin_amdgcn_ballot_w64(c7) &
+                                (one_chunk ? jokm : __builtin_amdgcn_ballot_w64(jok));
+          if (mask == 0) continue;
+          const int b = b0 + bo;
+          const T bar = inc < bE ? inc : bE;  // an energy to beat
+          T E;
+          bool valid = feas;   // E is the candidate's energy
+          if constexpr (CONT) {
+            // with every offloader at the first one's frequency, the lowest
+            const T pj = one_chunk ? pj1 : sP[jok ? j : 0];
+            const T lb = fma_(pj, Phi, fma_(T(b), least_cpu(Cs, kC, H - up0, f0), r.esl));
+            const uint64_t need = mask & ~__builtin_amdgcn_ballot_w64(beaten(lb, bar));
+            if (need == 0) continue;
+            valid = feas & !beaten(lb, bar);
+            const int hi = 63 - __clzll((long long)need);
+            const int bpass = b0 + __builtin_amdgcn_readlane(bo, hi);  // largest b needed
+            const T Hu = feas ? H : inf_of<T>();
+            const T f2 = (Cs > T(0)) ? cont_sum_f2(sup, Hu, b, b0, bpass, Cs, fmin, fmax) : T(0);
+            E = fma_(pj, Phi, fma_(kC, f2, r.esl));
           } else {
-            bool mv = q0.t > x0;
-            if (__builtin_amdgcn_ballot_w64(mv)) {
-              do {
-                p0 += mv ? 1 : 0;
-                q0 = *p0;
-                mv = q0.t > x0;
-              } while (__builtin_amdgcn_ballot_w64(mv));
+            // Eq. (20) for the first offloader: the number of levels too slow
+            // for its budget (latency falls with the level), by steps up from
+            // the level of the lane's previous pass with one chunk (a binary
+            // search on the first pass measured slower), else by binary search
+            // (an infeasible lane's budget is +inf: level 0, no steps)
+            const T x0 = (feas ? H : inf_of<T>()) - up0;
+            if (!one_chunk) {
+              const Level<T> *c0 = ste - 1;  // one before the first level that fits
+              for (int step = K2 >> 1; step > 0; step >>= 1)
+                c0 += (c0[step].t > x0) ? step : 0;
+              p0 = c0 + 1;
+              q0 = *p0;
+            } else {
+              bool mv = q0.t > x0;
+              if (__builtin_amdgcn_ballot_w64(mv)) {
+                do {
+                  p0 += mv ? 1 : 0;
+                  q0 = *p0;
+                  mv = q0.t > x0;
+                } while (__builtin_amdgcn_ballot_w64(mv));
+              }
+            }
+            // When the last offloader fits the first one's level, every
+            // offloader runs at it (the levels rise along pi): b of its energy.
+            E = fma_(one_chunk ? pj1 : sP[jok ? j : 0], Phi, T(b) * q0.e + r.esl);
+            // Otherwise that is a bound: the others' levels are higher.
+            const bool up_last = q0.t > hl;
+            valid = feas & !up_last;
+            const bool open = up_last & !beaten(E, bar);
+            const uint64_t mm = mask & __builtin_amdgcn_ballot_w64(open);
+            if (!QUEUE && mm) {
+              // Otherwise, in short batches, the CPU part of Eq. (21) by runs
+              // of equal level: a walk over the users, four per broadcast read
+              // (user 0 is at level p0), until every such lane is at a level
+              // that fits its last offloader.  Users below b0 belong to every
+              // lane's batch; past a lane's batch the budget is +inf.  The
+              // other lanes get an infinite budget and drop the result.
+              const bool walk = feas & open;
+              const T Hm = walk ? H : inf_of<T>();
+              const T hm = walk ? hl : inf_of<T>();
+              const int bw = b0 + __builtin_amdgcn_readlane(bo, 63 - __clzll((long long)mm));
+              const Level<T> *lv = p0;
+              T tk = q0.t;
+              T acc = T(0);
+              int run = 0;  // first user of the current level
+              int g = 0;
+              for (; g + 4 <= b0; g += 4) {
+                if (!__builtin_amdgcn_ballot_w64(tk > hm)) break;
+                const Quad<T> c = *(const Quad<T> *)(sup + g);
+                JDOB_USER(Hm - c.v[0], g);
+                JDOB_USER(Hm - c.v[1], g + 1);
+                JDOB_USER(Hm - c.v[2], g + 2);
+                JDOB_USER(Hm - c.v[3], g + 3);
+              }
+              for (; g < bw; ++g) {
+                if (!__builtin_amdgcn_ballot_w64(tk > hm)) break;
+                const T u = sup[g];
+                const T Hg = (g < b) ? Hm : inf_of<T>();
+                JDOB_USER(Hg - u, g);
+              }
+              acc = fma_(T(b - run), lv->e, acc);
+              const T Ew = fma_(one_chunk ? pj1 : sP[jok ? j : 0], Phi, acc + r.esl);
+              E = walk ? Ew : E;
+              valid |= walk;
+            } else if (QUEUE && mm) {
+              // the candidate joins the queue
+              const bool multi = feas & open;
+              const int slot = qtail + (int)__builtin_amdgcn_mbcnt_hi(
+                                           (uint32_t)(mm >> 32),
+                                           __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u));
+              if (multi)
+                sq[slot & (QCAP - 1)] =
+                    (uint32_t)b | ((uint32_t)j << 11) | ((uint32_t)(p0 - ste) << 19);
+              qtail += __builtin_popcountll(mm);
+              if (qtail - qhead >= WAVE) flush(WAVE);  // (QUEUE only)
             }
           }
-          // When the last offloader fits the first one's level, every
-          // offloader runs at it (the levels rise along pi): b of its energy.
-          E = fma_(one_chunk ? pj1 : sP[jok ? j : 0], Phi, T(b) * q0.e + r.esl);
-          // Otherwise that is a bound: the others' levels are higher.
-          const bool up_last = q0.t > hl;
-          valid = feas & !up_last;
-          const bool open = up_last & !beaten(E, bar);
-          const uint64_t mm = mask & __builtin_amdgcn_ballot_w64(open);
-          if (!QUEUE && mm) {
-            // Otherwise, in short batches, the CPU part of Eq. (21) by runs
-            // of equal level: a walk over the users, four per broadcast read
-            // (user 0 is at level p0), until every such lane is at a level
-            // that fits its last offloader.  Users below b0 belong to every
-            // lane's batch; past a lane's batch the budget is +inf.  The
-            // other lanes get an infinite budget and drop the result.
-            const bool walk = feas & open;
-            const T Hm = walk ? H : inf_of<T>();
-            const T hm = walk ? hl : inf_of<T>();
-            const int bw = b0 + __builtin_amdgcn_readlane(bo, 63 - __clzll((long long)mm));
-            const Level<T> *lv = p0;
-            T tk = q0.t;
-            T acc = T(0);
-            int run = 0;  // first user of the current level
-            int g = 0;
-            for (; g + 4 <= b0; g += 4) {
-              if (!__builtin_amdgcn_ballot_w64(tk > hm)) break;
-              const Quad<T> c = *(const Quad<T> *)(sup + g);
-              JDOB_USER(Hm - c.v[0], g);
-              JDOB_USER(Hm - c.v[1], g + 1);
-              JDOB_USER(Hm - c.v[2], g + 2);
-              JDOB_USER(Hm - c.v[3], g + 3);
-            }
-            for (; g < bw; ++g) {
-              if (!__builtin_amdgcn_ballot_w64(tk > hm)) break;
-              const T u = sup[g];
-              const T Hg = (g < b) ? Hm : inf_of<T>();
-              JDOB_USER(Hg - u, g);
-            }
-            acc = fma_(T(b - run), lv->e, acc);
-            const T Ew = fma_(one_chunk ? pj1 : sP[jok ? j : 0], Phi, acc + r.esl);
-            E = walk ? Ew : E;
-            valid |= walk;
-          } else if (QUEUE && mm) {
-            // the candidate joins the queue
-            const bool multi = feas & open;
-            const int slot = qtail + (int)__builtin_amdgcn_mbcnt_hi(
-                                         (uint32_t)(mm >> 32),
-                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u));
-            if (multi)
-              sq[slot & (QCAP - 1)] =
-                  (uint32_t)b | ((uint32_t)j << 11) | ((uint32_t)(p0 - ste) << 19);
-            qtail += __builtin_popcountll(mm);
-            if (qtail - qhead >= WAVE) flush(WAVE);  // (QUEUE only)
+          if (one_chunk) {
+            // (of equal energies the larger batch, the lower flat index)
+            const bool take = valid & (CONT ? (E < bE) | ((E == bE) & (b > bI)) : E <= bE);
+            bE = take ? E : bE;
+            bI = take ? b : bI;
+            lower_inc(take, E);
+          } else {
+            const int idx = sJN + (J - 1 - j) * N + (N - b);
+            const bool take = valid & better(E, idx, bE, bI);
+            bE = take ? E : bE;
+            bI = take ? idx : bI;
+            lower_inc(take, E);
           }
         }
-        if (one_chunk) {
-          // (of equal energies the larger batch, the lower flat index)
-          const bool take = valid & (CONT ? (E < bE) | ((E == bE) & (b > bI)) : E <= bE);
-          bE = take ? E : bE;
-          bI = take ? b : bI;
-          lower_inc(take, E);
-        } else {
-          const int idx = sJN + (J - 1 - j) * N + (N - b);
-          const bool take = valid & better(E, idx, bE, bI);
-          bE = take ? E : bE;
-          bI = take ? idx : bI;
-          lower_inc(take, E);
-        }
-      }
       }
       c0 = next;
     }
@@ -1694,7 +1740,10 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_solve_kernel(SolveArgs<T> args) 
   const T tfree = p.tfree ? p.tfree[inst] : T(0);
   int bmin;
   bool any = true;  // some partition point may have a feasible candidate
-  if (FROM_TABLES)
+  const bool flags = !FROM_TABLES || one_per_lane(p);
+  if (FROM_TABLES && flags)
+    any = prepare_lanes<T, FROM_TABLES, CONT, COUNT>(p, tab, inst, smem, y, lane, tfree, bmin);
+  else if (FROM_TABLES)
     prepare_instance<T, FROM_TABLES, CONT>(p, tab, inst, smem, y, lane, bmin);
   else
     any = prepare_fused<T, CONT, COUNT>(p, inst, smem, y, lane, tfree, bmin);
@@ -1717,7 +1766,7 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_solve_kernel(SolveArgs<T> args) 
     search_candidates<T, FROM_TABLES, ONE_CHUNK, COUNT, GREEDY, CONT, QUEUE>(
         p, tab, inst, smem, y, lane, N, blo, tfree, uni(bmin) == 0 ? uni(sSL[0]) : inf_of<T>(),
         GpuCost<T>(p.gf, sr, sP, p.j_low, J, p.gopt, p.gc, p.p0), bestE, bestI, nfeas, nevals,
-        !FROM_TABLES);
+        flags);
 
   // local computing competes last
   const int idxLC = L * J * N;

@@ -338,7 +338,9 @@ template <typename T> struct GpuCost {
 };
 
 // The frequency at which a second of top-level batch latency costs least.
-inline double best_gpu_freq(double gc, double p0) { return gc > 0 ? cbrt(p0 / (2.0 * gc)) : INFINITY; }
+inline double best_gpu_freq(double gc, double p0) {
+  return gc > 0 ? cbrt(p0 / (2.0 * gc)) : INFINITY;
+}
 
 // A copy of a uniform value in scalar registers of its own.  Kernel arguments
 // arrive in wide loads (eight or sixteen registers at a time); without the

@@ -111,7 +111,12 @@ __host__ __device__ inline HLayout make_hlayout(int N, int L, int K, int J, int 
                                                bool grouped) {
   HLayout y;
   int o = 0, lim = 0;  // (the limit also counts a row of rank keys)
-  auto take = [&](int bytes) { int r = o; o = align8(o + bytes); lim = align8(lim + bytes); return r; };
+  auto take = [&](int bytes) {
+    int r = o;
+    o = align8(o + bytes);
+    lim = align8(lim + bytes);
+    return r;
+  };
   auto take32 = [&](int bytes) {
     o = (o + 31) & ~31;
     lim = (lim + 31) & ~31;
@@ -168,7 +173,10 @@ __host__ __device__ inline HLayout make_hlayout(int N, int L, int K, int J, int 
   y.limit = lim;
   y.tab = -1;
   const int base = (o + 31) & ~31, tab_bytes = L * N * 4 * szT;
-  auto per_cu = [](int bytes) { const int w = LDS_PER_CU / (bytes > 0 ? bytes : 1); return w < 24 ? w : 24; };
+  auto per_cu = [](int bytes) {
+    const int w = LDS_PER_CU / (bytes > 0 ? bytes : 1);
+    return w < 24 ? w : 24;
+  };
   if (grouped && base + tab_bytes <= LDS_LIMIT && per_cu(base + tab_bytes) == per_cu(o))
     y.tab = take32(tab_bytes);
   y.total = o;
