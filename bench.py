@@ -7,15 +7,15 @@ rows, the candidate grid with deadline masking, per-user levels and energy,
 the argmin and the winner's policy), with the inputs resident in HBM.
 
 Prints ONE JSON line:
-  value   = candidate policies evaluated per second (every (s, j, b) of
-            L*J*N plus local computing counts once its feasibility is decided)
+  value   = candidate policies decided per second (every (s, j, b) of L*J*N
+            plus local computing counts: evaluated, or excluded by its
+            deadline or by a lower bound of its energy)
   roofline: the solve kernel against the FP32 VALU issue rate (it is a loop
             of compares, selects and adds: no dense contraction, and HBM
-            traffic is ~1 KB per instance); "achieved" counts the method's
-            algorithmic operations (14 per feasible candidate, 2 +
-            ceil(log2(K+1)) per offloader evaluation), "useful_work" the
-            stricter count of what this kernel cannot avoid, and
-            valu_busy_counter the measured fraction of VALU issue slots
+            traffic is ~1 KB per instance); "achieved" counts the options that
+            the solved user sets are decided from, each computed once (4 per
+            user, 3 per CPU level and 4 per GPU level of every partition
+            point), and valu_busy_counter the measured fraction of VALU issue slots
             used (SQ_ACTIVE_INST_VALU less the dual-issue slots), with the
             counter-classified FP32/INT32 lane-op rates in valu_counters
   cpu_baseline: the CPU oracle, single thread pinned to one core, on a
@@ -46,40 +46,30 @@ sys.path.insert(0, ROOT)
 # VALU lane-operations per second.
 VALU_PEAK_OPS = 256 * 4 * 16 * 2.4e9
 HBM_PEAK = 8.0e12
-# Algorithmic lane-operations of the method (the roofline's "achieved"),
-# for the work the kernel evaluates candidate by candidate:
-#   per feasible candidate: batch latency 3, slack 1, the three tests 4, GPU
-#   energy 1, total 2-3, argmin 2 = 14;
-#   per offloader evaluation of a feasible candidate: the budget subtract, a
-#   search of its lowest fitting level among K (ceil(log2(K+1)) compares)
-#   and the energy add; with a continuous CPU frequency: subtract,
-#   reciprocal, multiply, clamp below, clamp above, square-and-add = 6.
-# Infeasible candidates are decided in bulk (a partition point that fails at
-# its most favourable candidate, a pass with no feasible lane); charging 14
-# to each of them would put "achieved" above the peak (c4: 25x).
-OPS_PER_CANDIDATE = 14
-OPS_PER_USER_EVAL_CONT = 6
-# The stricter count of the work this kernel cannot avoid ("useful work"):
-# 16 per feasible candidate (infeasible ones are mostly decided in bulk) and
-# 3 per offloader evaluation (subtract, one compare against the lane's
-# current level, add: the levels only move up along the users); with
-# heterogeneous users the level is searched in each user's own table.
-USEFUL_PER_FEASIBLE_CAND = 16
-USEFUL_PER_USER_EVAL = 3
+# Algorithmic lane-operations (the roofline's "achieved"): the options of
+# Eqs. (1)-(5) that every solved user set is decided from, each computed once.
+# Per partition point, per user the upload latency and energy, the budget and
+# a comparison; per CPU level (with heterogeneous users: of each user) its
+# latency, energy and a comparison; per GPU level the batch latency, its
+# stretch, the energy and a comparison.  The candidates built from them are not
+# charged: the kernel drops nearly all by lower bounds (a count of 14 per
+# feasible candidate and 7 per offloader evaluation would put "achieved" at
+# seven times the peak at c3).
+OPS_PER_USER = 4
+OPS_PER_CPU_LEVEL = 3
+OPS_PER_GPU_LEVEL = 4
 
 
-def model_ops_per_user_eval(w, mode) -> int:
-    if mode & MODE_BITS["continuous"]:
-        return OPS_PER_USER_EVAL_CONT
-    return 2 + int(np.ceil(np.log2(w.K + 1)))
-
-
-def useful_ops_per_user_eval(w, mode) -> int:
-    if mode & MODE_BITS["continuous"]:
-        return OPS_PER_USER_EVAL_CONT
-    if w.users is not None:
-        return 2 + int(np.ceil(np.log2(w.K + 1)))
-    return USEFUL_PER_USER_EVAL
+def option_ops(w, mode: int, grouped: bool) -> int:
+    """Lane-operations per launch by the model above; the grouping solves
+    every run of the deadline order."""
+    cuts = 1 if mode & MODE_BITS["binary"] else w.L
+    levels = 1 if mode & MODE_BITS["fixed-edge"] else w.J
+    K = 2 if mode & MODE_BITS["continuous"] else w.K
+    sizes = [n for n in range(1, w.N + 1) for _ in range(w.N - n + 1)] if grouped else [w.N]
+    per = sum(OPS_PER_USER * n + OPS_PER_CPU_LEVEL * K * (n if w.users is not None else 1)
+              + OPS_PER_GPU_LEVEL * levels for n in sizes)
+    return w.num_instances * cuts * per
 
 
 def log(*a):
@@ -470,7 +460,7 @@ def main():
     else:
         solve, alloc = jdob.solve_batch, jdob.alloc_policy
     # one untimed launch that also fills the optional work counters (feasible
-    # candidates and user evaluations, for the roofline); the timed launches
+    # candidates and user evaluations); the timed launches
     # request only the policy
     counted = solve(d, alloc(d, counters=True))
     out = alloc(d, counters=False)
@@ -508,9 +498,8 @@ def main():
     U = int(hc["num_user_evals"].sum())
     cand_per_inst = grouped_family_size(w, mode) if grouped else family_size(w, mode)
     cands = I * cand_per_inst
-    ops = OPS_PER_CANDIDATE * F + model_ops_per_user_eval(w, mode) * U
+    ops = option_ops(w, mode, grouped)
     achieved = ops / (kmean * 1e-3)
-    useful = USEFUL_PER_FEASIBLE_CAND * F + useful_ops_per_user_eval(w, mode) * U
     in_bytes, out_bytes = algorithmic_bytes(w, grouped, cont)
 
     tag = w.name if mode == w.mode else f"{w.name}_{args.mode.replace('+', '_')}"
@@ -564,14 +553,8 @@ def main():
                      "valu_counters": counters.get("valu"),
                      "kernel": kernel,
                      "ops_per_launch": ops,
-                     "ops_model": f"{OPS_PER_CANDIDATE} per feasible candidate + "
-                                  f"{model_ops_per_user_eval(w, mode)} per offloader evaluation",
-                     "useful_work": {"ops_per_launch": useful,
-                                     "achieved": useful / (kmean * 1e-3) / 1e12,
-                                     "frac": useful / (kmean * 1e-3) / VALU_PEAK_OPS,
-                                     "model": f"{USEFUL_PER_FEASIBLE_CAND} per feasible candidate + "
-                                              f"{useful_ops_per_user_eval(w, mode)} per offloader "
-                                              "evaluation"},
+                     "ops_model": f"per partition point and solved user set: {OPS_PER_USER} per user, "
+                                  f"{OPS_PER_CPU_LEVEL} per CPU level, {OPS_PER_GPU_LEVEL} per GPU level",
                      "hbm_algorithmic_bytes": in_bytes + out_bytes,
                      "hbm_frac": (in_bytes + out_bytes) / (kmean * 1e-3) / HBM_PEAK},
         "cpu_baseline": None,
