@@ -683,7 +683,8 @@ __device__ bool prepare_lanes(const Problem<T> &p, const Tables<T> &tab, int64_t
     if (lane >= p.j_low && lane < J) rho = P * (gtop * rough_rcp(g));
     rho = wave_min(rho) * T(1.0 - 0x1p-20);
     const T lc = lane_read(run_reduce(ism ? eL : T(0), 6, add), 0);
-    quads[lane] = ism ? eL : T(0);
+    // (the batch records' room holds 4 (N + 2) entries and more, fewer than the wave's lanes for few users)
+    if (lane < ((N + 3) & ~3)) quads[lane] = ism ? eL : T(0);
     __syncthreads();
     const int lg = lanes_per_item(p.s_end), s = lane >> lg;
     const int sc = s < p.s_end ? s : 0;
@@ -968,8 +969,8 @@ __device__ bool prepare_fused(const Problem<T> &p, int64_t inst, unsigned char *
     if (bmin == 0) {  // local computing is the only candidate: its ranking energy
       T e = T(0);
       for (int m = lane; m < N; m += WAVE) e = e + seL[m];
-      e = wave_iscan(e, T(0), [](T a, T b) { return a + b; });
-      if (lane == 0) sSL[0] = lane_read(e, WAVE - 1);
+      e = lane_read(wave_iscan(e, T(0), [](T a, T b) { return a + b; }), WAVE - 1);
+      if (lane == 0) sSL[0] = e;
     }
     __syncthreads();
     return false;

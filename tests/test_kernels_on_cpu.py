@@ -1,0 +1,108 @@
+"""The kernels' sources compiled for the CPU (tests/wave_cpu: one wave of 64
+lanes, LDS blocks of exactly the launch's length) and run against the oracle
+at small sizes: a store past a launch's LDS, LDS that one lane overwrites
+before another has read it (the lanes run one after the other between two
+synchronisations, lowest first and highest first), or LDS read before it is
+written ends the run or changes a result.  Every run is a process of its own.
+The comparison is tests/parity.py's."""
+
+import json
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2504_14611_amd", "csrc")
+CLANG = "/opt/rocm/llvm/bin/clang++"
+
+CHILD = r"""
+import json, sys
+sys.path.insert(0, __ROOT__)
+import numpy as np
+import oracle
+from paper_2504_14611_amd import jdob
+from paper_2504_14611_amd import workloads as W
+from tests.parity import compare
+from tests.test_gpu_grouped import compare_grouped
+lib = jdob.load(__SO__)
+
+def joint(d, **k):
+    return jdob.eval_joint(d, jdob.eval_user_tables(d, stream=0), **k)
+
+for n, c in enumerate(json.loads(sys.stdin.read())):
+    print(c, flush=True)
+    p = W.generate(W.WORKLOADS[c["base"]].replace(name="cpu", stream=c.get("stream", 8600), num_instances=c.get("I", 2),
+                                                  dtype=c.get("dtype", "f32"), **c["kw"]))
+    p["mode"] = int(p["mode"]) | c.get("mode", 0) if c.get("keep_mode", True) else c.get("mode", 0)
+    for k, f in c.get("scale", {}).items():
+        p[k] = float(p[k] * f) if np.isscalar(p[k]) else (p[k] * p[k].dtype.type(f)).astype(p[k].dtype)
+    for k, v in c.get("fill", {}).items():
+        p[k] = np.full_like(p[k], v)
+    grouped = c.get("grouped", False)
+    ora = oracle.solve_grouped(p, threads=4) if grouped else oracle.solve(p, threads=4)
+    d = jdob.to_device(p, "cpu")
+    calls = [jdob.solve_grouped] if grouped else [jdob.solve_batch]
+    if not grouped and p.get("user_zeta") is None:
+        calls.append(joint)
+    for down in (0, 1):
+        lib.wave_cpu_descending(down)
+        for call in calls:
+            for counters in (False, True):
+                got = jdob.to_host(call(d, stream=0, counters=counters, freq=True))
+                label = f"{call.__name__} counters={counters} descending={down}"
+                compare_grouped(p, got, ora, label) if grouped else compare(p, got, ora, label=label)
+print("RUN COMPLETE", flush=True)
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    """Builds the library once; returns a function that runs a list of cases."""
+    tmp = tmp_path_factory.mktemp("wave_cpu")
+    for f in os.listdir(CSRC):
+        src = open(os.path.join(CSRC, f)).read()
+        # what a header cannot define away: LDS, address spaces, empty asm that pins registers
+        src = re.sub(r"extern __shared__[^;]*?(\w+)\[\];", r"unsigned char *const \1 = wave_cpu::lds();", src)
+        src = re.sub(r'asm volatile\("" :[^;]*\);', "", src).replace("__attribute__((address_space(4)))", "")
+        (tmp / f.replace(".hip", ".cpp")).write_text(src)
+    objs = [str(f) for f in sorted(tmp.glob("*.cpp"))]
+    flags = ["-O1", "-std=c++17", "-fPIC", "-ffp-contract=off", "-w", "-I", os.path.join(ROOT, "tests", "wave_cpu"),
+             "-I", os.path.join(ROOT, "include")]
+    procs = [subprocess.Popen([CLANG, *flags, "-c", f, "-o", f + ".o"]) for f in objs]
+    assert all([p.wait() == 0 for p in procs])
+    so = str(tmp / "libjdob_cpu.so")
+    subprocess.run([CLANG, "-shared", "-o", so, *[f + ".o" for f in objs]], check=True)
+    code = CHILD.replace("__ROOT__", repr(ROOT)).replace("__SO__", repr(so))
+
+    def go(cases):
+        r = subprocess.run([sys.executable, "-c", code], input=json.dumps(cases), capture_output=True, text=True,
+                           timeout=600)
+        assert r.returncode == 0 and "RUN COMPLETE" in r.stdout, \
+            f"exit {r.returncode}\n{r.stdout[-600:]}\n{r.stderr[-3000:]}"
+    return go
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("mode", [0, 1, 2, 8])
+def test_few_users_stay_in_the_launch(run, mode, dtype):
+    """The rows of few users are the shortest: at 1 to 17 users and GPU levels
+    on both sides of every count of batch records."""
+    run([dict(base=base, mode=mode, dtype=dtype, kw=dict(N=N, L=1 + N % 4, K=4, J=J))
+         for N in (1, 2, 3, 4, 5, 6, 9, 10, 12, 13, 16, 17)
+         for J in (1, 2, 5, 8, 16, 31, 33, 48, 64, 65) for base in ("c2",)])
+
+
+SHAPES = [dict(base="p4a", kw=dict(N=10, L=22, K=4, J=32)), dict(base="c2b", kw=dict(N=20, L=22, K=8, J=9)),
+          dict(base="c3", kw=dict(N=32, L=22, K=16, J=32)), dict(base="c4b", kw=dict(N=64, L=63, K=8, J=16)),
+          dict(base="c4b", kw=dict(N=70, L=20, K=8, J=40)), dict(base="p4b", kw=dict(N=130, L=9, J=65)),
+          dict(base="p4b", kw=dict(N=9, L=70, J=5)),
+          dict(base="g10", grouped=True, kw=dict(N=7, L=6, K=5, J=9)),
+          dict(base="p5", grouped=True, kw=dict(N=5, L=3, J=33))]
+
+
+@pytest.mark.parametrize("k", range(len(SHAPES)))
+def test_shapes(run, k):
+    run([dict(SHAPES[k], mode=mode, dtype=dtype) for mode in (0, 1, 2, 4) for dtype in ("f32", "f64")])
