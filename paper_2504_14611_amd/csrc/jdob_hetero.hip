@@ -452,6 +452,7 @@ __device__ void hbounds(const HProblem<T> &p, unsigned char *smem, const HLayout
       T g;
       const HPos<T> v = user_at(smem, y, K, s, in ? q : 0, &g);
       const int pos = gamma_rank(g, in, N, lg, (uint64_t *)(smem + y.bt), lane);
+      __syncthreads();  // every lane has read the keys before a record takes their room
       if (in) scratch[(lane - q) + pos] = v;
       __syncthreads();
       u = scratch[in ? lane : 0];

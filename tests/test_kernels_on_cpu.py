@@ -106,3 +106,16 @@ SHAPES = [dict(base="p4a", kw=dict(N=10, L=22, K=4, J=32)), dict(base="c2b", kw=
 @pytest.mark.parametrize("k", range(len(SHAPES)))
 def test_shapes(run, k):
     run([dict(SHAPES[k], mode=mode, dtype=dtype) for mode in (0, 1, 2, 4) for dtype in ("f32", "f64")])
+
+
+HETERO = [dict(base="h1", kw=dict(N=12, L=6, K=5, J=9)), dict(base="h1", kw=dict(N=16, L=66, K=3, J=4)),
+          dict(base="h2", kw=dict(N=30, L=7, J=33)), dict(base="h2", kw=dict(N=63, L=5, J=12)),
+          dict(base="h5", grouped=True, kw=dict(N=6, L=5, J=8)),
+          dict(base="h1", grouped=True, I=1, kw=dict(N=10, L=60, K=5, J=8))]
+
+
+@pytest.mark.parametrize("k", range(len(HETERO)))
+def test_heterogeneous_users(run, k):
+    """Several partition points' gamma orders are formed in one room: keys,
+    then records."""
+    run([dict(HETERO[k], mode=mode, dtype=dtype) for mode in (0, 1, 4, 8) for dtype in ("f32", "f64")])
