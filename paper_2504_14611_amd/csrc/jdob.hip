@@ -1375,6 +1375,7 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
     // that fits the last offloader ends the batch).  The same operations as
     // the pass give the same budgets.
     auto flush = [&](int cnt) {
+      __syncthreads();  // the pass that filled the queue has stored its entries
       const bool act = lane < cnt;
       const uint32_t e = sq[(qhead + (act ? lane : 0)) & (QCAP - 1)];
       const int b = act ? (int)(e & 2047u) : 0;

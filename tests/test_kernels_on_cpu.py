@@ -119,3 +119,16 @@ def test_heterogeneous_users(run, k):
     """Several partition points' gamma orders are formed in one room: keys,
     then records."""
     run([dict(HETERO[k], mode=mode, dtype=dtype) for mode in (0, 1, 4, 8) for dtype in ("f32", "f64")])
+
+
+QUEUED = [dict(base="c4b", kw=dict(N=33, L=9, K=8, J=16)), dict(base="c4b", kw=dict(N=100, L=22, K=8, J=64)),
+          dict(base="c2b", kw=dict(N=33, L=9, K=8, J=8)), dict(base="c2b", kw=dict(N=20, L=22, K=16, J=65)),
+          dict(base="c2b", kw=dict(N=70, L=9, K=8, J=16))]
+
+
+@pytest.mark.parametrize("k", range(len(QUEUED)))
+def test_queue_of_candidates(run, k):
+    """A full queue of candidates is evaluated in the pass that filled it.
+    (Cheap uploads and GPU levels leave many candidates to evaluate.)"""
+    run([dict(QUEUED[k], dtype=dtype, mode=0, stream=8700 + n, scale=dict(deadline=a, p_tx=b, gpu_c=b, gpu_p_static=b))
+         for dtype in ("f32", "f64") for n in range(3) for a in (0.7, 1.0, 1.5) for b in (0.01, 0.1)])
