@@ -260,6 +260,13 @@ template <typename T> __device__ inline bool beaten(T lb, T inc) {
   return lb * T(1.0 - 0x1p-12) > inc;
 }
 
+// A bound that overflows still belongs to a feasible candidate, whose energy
+// may be infinite: it stays below the +inf of those that are not.
+__device__ inline float finite_bound(float lb) { return lb < 0x1.fffffep127f ? lb : 0x1.fffffep127f; }
+__device__ inline double finite_bound(double lb) {
+  return lb < 0x1.fffffffffffffp1023 ? lb : 0x1.fffffffffffffp1023;
+}
+
 // Hardware reciprocal, for bounds.
 __device__ inline float rough_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ inline double rough_rcp(double x) { return __builtin_amdgcn_rcp(x); }

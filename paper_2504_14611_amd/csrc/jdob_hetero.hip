@@ -487,16 +487,19 @@ __device__ void hbounds(const HProblem<T> &p, unsigned char *smem, const HLayout
       const T o = __shfl_down(sl, 1, W);
       sl = q + 1 < W ? o : T(0);
     }
-    // (sl is infinite where a user left local misses its deadline, (8))
-    const bool ok = mem & (H >= tfree) & (H >= nd) & (sl < inf_of<T>());
+    // no user left local may miss its deadline, (8)
+    const uint64_t late =
+        __builtin_amdgcn_ballot_w64(mem && ((const int *)(smem + y.kL))[m] < 0) >> (lane - q);
+    const bool ok =
+        mem & (H >= tfree) & (H >= nd) & ((((late & (~uint64_t(0) >> (WAVE - W))) >> q) >> 1) == 0);
     if constexpr (COUNT) {
       const int c = feasible_levels(p, sr, lo, nd, ab, tfree);
       nfeas += ok ? c : 0;
       nevals += ok ? c * b : 0;
     }
     const T room = lo - (nd > tfree ? nd : tfree);
-    const T lb = run_reduce(ok ? gpu.least(ab, room, lo) + (off + sl) : inf_of<T>(), lg,
-                            [](T a, T b) { return b < a ? b : a; });
+    const T lb = run_reduce(ok ? finite_bound(gpu.least(ab, room, lo) + (off + sl)) : inf_of<T>(),
+                            lg, [](T a, T b) { return b < a ? b : a; });
     if (q == 0 && s0 + r < p.s_end) slb[s0 + r] = lb;
     __syncthreads();
   }
@@ -569,7 +572,7 @@ __device__ int hrow(const HProblem<T> &p, int64_t inst, unsigned char *smem, con
   const T cl =
       run_iscan(in ? least_cpu(us.z, skc[lane], Htop - us.up, us.fmin) : T(0), T(0), lg, add);
   const T lb = gpu.least(ab, lo - (nd > tfree ? nd : tfree), lo) + (esl + cl);
-  *rb = (ok >> lane) & 1 ? lb : inf_of<T>();
+  *rb = (ok >> lane) & 1 ? finite_bound(lb) : inf_of<T>();
   *todo = ok & ~__builtin_amdgcn_ballot_w64(beaten(lb, inc));
   if (!*todo) return bmin;
   if (in) {
