@@ -272,14 +272,14 @@ __device__ inline float rough_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ inline double rough_rcp(double x) { return __builtin_amdgcn_rcp(x); }
 
 // A little less than 1 / x (x > 0; the hardware's reciprocal of a denormal is
-// infinite).
+// infinite), small enough for the sum over JDOB_MAX_USERS users.
 __device__ inline float rcp_below(float x) {
   const float q = rough_rcp(x) * (1.0f - 0x1p-20f);
-  return q < 0x1p126f ? q : 0x1p126f;
+  return q < 0x1p116f ? q : 0x1p116f;
 }
 __device__ inline double rcp_below(double x) {
   const double q = rough_rcp(x) * (1.0 - 0x1p-20);
-  return q < 0x1p1022 ? q : 0x1p1022;
+  return q < 0x1p1012 ? q : 0x1p1012;
 }
 
 // CPU energy kC * f^2 (kC = kappa * C[s]) of a user with budget x or less, from

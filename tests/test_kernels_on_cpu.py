@@ -150,3 +150,11 @@ def test_heterogeneous_energies_that_overflow(run, base, kw):
     run([dict(base=base, mode=mode, kw=kw, I=12, stream=8800 + f, keep_mode=False, overflow=True,
               scale=dict(cycles=f * 1e9, user_local_freq=f * 1e9, local_freq=f * 1e9, user_kappa=1e-8, kappa=1e-8))
          for mode in (0, 1, 2) for f in (5, 10, 12, 16)])
+
+
+@pytest.mark.parametrize("base", ["c2b", "p4b"])
+def test_rates_without_a_reciprocal(run, base):
+    """Nothing to upload over links whose rates are denormal numbers: the
+    upload takes no time, and offloading is feasible."""
+    run([dict(base=base, kw=dict(N=N, L=9, K=4, J=8), I=32, stream=7001, keep_mode=False, mode=mode,
+              fill=dict(bits=0.0, rate=1e-40)) for N in (3, 8, 20) for mode in (0, 1, 8)])
