@@ -262,9 +262,11 @@ template <typename T> __device__ inline bool beaten(T lb, T inc) {
 
 // A bound that overflows still belongs to a feasible candidate, whose energy
 // may be infinite: it stays below the +inf of those that are not.
-__device__ inline float finite_bound(float lb) { return lb < 0x1.fffffep127f ? lb : 0x1.fffffep127f; }
-__device__ inline double finite_bound(double lb) {
-  return lb < 0x1.fffffffffffffp1023 ? lb : 0x1.fffffffffffffp1023;
+__device__ inline float finite_bound(float lb, float part = 1) {
+  return lb < 0x1.fffffep127f * part ? lb : 0x1.fffffep127f * part;
+}
+__device__ inline double finite_bound(double lb, double part = 1) {
+  return lb < 0x1.fffffffffffffp1023 * part ? lb : 0x1.fffffffffffffp1023 * part;
 }
 
 // Hardware reciprocal, for bounds.

@@ -431,10 +431,13 @@ __device__ inline int feasible_levels(const HProblem<T> &p, const T *sr, T lo, T
 // falls with b and rises with j, so the test is that of the top GPU level.
 // (16 users, 22 layers: 5.5 of 21.5 partition points with feasible candidates
 // are then searched, best bound first; 13 of the batches of 72 passes.)
-// Counts the feasible candidates into nfeas, nevals when COUNT.
+// Counts the feasible candidates into nfeas, nevals when COUNT.  (Inlined: as
+// a function it kept its arguments in 1 KB of scratch a lane; grouping of 531 x
+// 21 users, binary64: 47 ms, 62 as a function.)
 template <typename T, bool COUNT>
-__device__ void hbounds(const HProblem<T> &p, unsigned char *smem, const HLayout &y, int lane,
-                        uint64_t mask, T tfree, const GpuCost<T> &gpu, T *slb, int &nfeas, int &nevals) {
+__device__ __forceinline__ void hbounds(const HProblem<T> &p, unsigned char *smem,
+                                        const HLayout &y, int lane, uint64_t mask, T tfree,
+                                        const GpuCost<T> &gpu, T *slb, int &nfeas, int &nevals) {
   const int N = p.N, K = p.K, J = p.J;
   const T *sC = (const T *)(smem + y.C), *sA = (const T *)(smem + y.A);
   const T *sB = (const T *)(smem + y.B), *sr = (const T *)(smem + y.r);
@@ -471,8 +474,10 @@ __device__ void hbounds(const HProblem<T> &p, unsigned char *smem, const HLayout
     const T off = run_iscan(mem ? fma_(((const T *)(smem + y.ptx))[m], u.up, cpu) : T(0), T(0), lg,
                             [](T a, T b) { return a + b; });
     // the others' local energy: suffix sums less the user's own
-    const T eL = mem ? ((const T *)(smem + y.eL))[m] : T(0);
-    T sl = eL;
+    // (infinite only for a user that misses its deadline: one whose energy
+    // overflows takes a value that 64 of cannot)
+    T sl = mem ? ((const T *)(smem + y.eL))[m] : T(0);
+    if (((const int *)(smem + y.kL))[m] >= 0) sl = finite_bound(sl, T(1) / WAVE);
     if (lg == 4) {
       sl = sl + dpp_mov<0x101, 0xf>(T(0), sl);  // row_shl:1
       sl = sl + dpp_mov<0x102, 0xf>(T(0), sl);
@@ -487,11 +492,8 @@ __device__ void hbounds(const HProblem<T> &p, unsigned char *smem, const HLayout
       const T o = __shfl_down(sl, 1, W);
       sl = q + 1 < W ? o : T(0);
     }
-    // no user left local may miss its deadline, (8)
-    const uint64_t late =
-        __builtin_amdgcn_ballot_w64(mem && ((const int *)(smem + y.kL))[m] < 0) >> (lane - q);
-    const bool ok =
-        mem & (H >= tfree) & (H >= nd) & ((((late & (~uint64_t(0) >> (WAVE - W))) >> q) >> 1) == 0);
+    // (sl is infinite where a user left local misses its deadline, (8))
+    const bool ok = mem & (H >= tfree) & (H >= nd) & (sl < inf_of<T>());
     if constexpr (COUNT) {
       const int c = feasible_levels(p, sr, lo, nd, ab, tfree);
       nfeas += ok ? c : 0;

@@ -218,6 +218,7 @@ template <typename A, typename... Rest> inline const void *first_arg(const A &a,
 #define __host__
 #define __align__(n) alignas(n)
 #define __launch_bounds__(...)
+#define __forceinline__ inline
 #define threadIdx (wave_cpu::Dim{(unsigned)wave_cpu::w().lane})
 #define blockIdx (wave_cpu::Dim{wave_cpu::w().block})
 #define gridDim (wave_cpu::Dim{wave_cpu::w().grid})
