@@ -1075,8 +1075,11 @@ __device__ inline T upload_time(const Problem<T> &p, const Tables<T> &tab, int64
 // in a queue and are evaluated 64 at a time, each run of equal level found
 // by binary search over the users; without it (few users) their runs are
 // summed by a walk over the users during the pass.
+// FEW: the partition points are searched as they come, those that pass the
+// test at the top GPU level, and the passes count their feasible candidates
+// (few_points).
 template <typename T, bool FROM_TABLES, bool ONE_CHUNK, bool COUNT, bool GREEDY, bool CONT,
-          bool QUEUE>
+          bool QUEUE, bool FEW = false>
 __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &tab, int64_t inst,
                                          unsigned char *smem, const Layout &y, int lane, int N,
                                          int blo, T tfree, T inc, const GpuCost<T> &gpu,
@@ -1150,6 +1153,14 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
       mv = tk > x;                                             \
     }                                                          \
   }
+
+  constexpr bool TALLY = COUNT && FEW;
+  auto tally = [&](bool feas, int b) {
+    if (TALLY) {
+      nfeas += feas ? 1 : 0;
+      nevals += feas ? b : 0;
+    }
+  };
 
   // inc, the lowest energy of a candidate known, after lanes with `take` found E
   auto lower_inc = [&](bool take, T E) {
@@ -1244,6 +1255,7 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
     const uint64_t mask = __builtin_amdgcn_ballot_w64(feas);
     if (mask == 0) return;
     const int b = bg;
+    tally(feas, b);
     // per half of the wave the highest feasible lane has the largest batch
     // and the lowest the smallest
     const uint64_t mlo = mask & 0xffffffffull, mhi = mask & ~0xffffffffull;
@@ -1436,12 +1448,12 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
         const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
         if (okm == 0) break;
         lb = ok ? lb : inf_of<T>();
-        todo = okm & ~__builtin_amdgcn_ballot_w64(beaten(lb, inc));
+        todo = TALLY ? okm : okm & ~__builtin_amdgcn_ballot_w64(beaten(lb, inc));
       }
       int next = c0 + WAVE;
       while (todo) {
         int q = __builtin_ctzll(todo);
-        if (CONT && nb == 1) {  // best bound first (no level is carried from pass to pass)
+        if (CONT && nb == 1 && !TALLY) {  // best bound first (no level is carried from pass to pass)
           const T m = wave_min(lb);
           if (!(m < inf_of<T>()) || beaten(m, inc)) break;
           q = __builtin_ctzll(__builtin_amdgcn_ballot_w64(lb == m));
@@ -1465,6 +1477,7 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
                                 (one_chunk ? jokm : __builtin_amdgcn_ballot_w64(jok));
           if (mask == 0) continue;
           const int b = b0 + bo;
+          tally(feas, b);
           const T bar = inc < bE ? inc : bE;  // an energy to beat
           T E;
           bool valid = feas;   // E is the candidate's energy
@@ -1583,7 +1596,7 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
     __syncthreads();
   };
 
-  if constexpr (COUNT && GREEDY) {
+  if constexpr (COUNT && GREEDY && !FEW) {
     // The work counters of the greedy family: the batch of each (s, j), found
     // by binary search over b with the test (7), if it meets the others.
     // Lanes take (s, j) pairs, several partition points at once where J leaves
@@ -1632,10 +1645,17 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
   for (int s0 = 0; s0 < s_end; s0 += WAVE) {
     uint64_t open = __builtin_amdgcn_ballot_w64(s0 + lane < s_end &&
                                                 (!flags_ready || sflag[s0 + lane]));
-    const bool bounds = (open & (open - 1) & ((open & (open - 1)) - 1)) != 0;  // three or more
+    if (FEW) {
+      // the test at the top GPU level and the smallest admissible batch
+      const int s = lane < s_end ? lane : 0, bc = blo <= N ? blo : N;
+      const T up = upload_time<T, FROM_TABLES>(p, tab, inst, sbits, srate, spi, s, bc - 1);
+      const T H = slo[bc] - (sA[s] + sB[s] * T(bc)) * rtop;
+      open &= __builtin_amdgcn_ballot_w64(blo <= N && H >= tfree && sC[s] / ftop <= H - up);
+    }
+    const bool bounds = !FEW && (open & (open - 1) & ((open & (open - 1)) - 1)) != 0;  // three or more
     T lb = inf_of<T>();
     const int lg = lanes_per_item(s_end), parts = 1 << lg, part = lane & (parts - 1);
-    if (bounds || (COUNT && !GREEDY && open)) {
+    if (bounds || (COUNT && !GREEDY && !FEW && open)) {
       T carry = T(0);
       for (int i0 = 0; i0 < N; i0 += WAVE) {
         const int i = i0 + lane;
@@ -2064,7 +2084,7 @@ __device__ inline void group_winner(const Problem<T> &p, int64_t inst, unsigned 
 // searches of small groups wait on LDS, and resident waves hide that
 // (measured: 65,536 instances of 10 users 5.15 ms at eight and seven waves,
 // 5.39 at six and five; 4,239 of 6 users 389, 380, 369 and 369 us).
-template <typename T, bool ONE_CHUNK, bool COUNT, bool GREEDY, bool CONT>
+template <typename T, bool ONE_CHUNK, bool COUNT, bool GREEDY, bool CONT, bool FEW>
 __global__ __launch_bounds__(WAVE, 7) void jdob_grouped_kernel(GroupedArgs<T> args) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x;
@@ -2115,7 +2135,7 @@ __global__ __launch_bounds__(WAVE, 7) void jdob_grouped_kernel(GroupedArgs<T> ar
   auto group_search = [&](int g, int bmin, T tf0, int &nf, int &ne) -> int {
     T bestE = inf_of<T>();
     int bestI = 0x7fffffff;
-    search_candidates<T, false, ONE_CHUNK, COUNT, GREEDY, CONT, false>(
+    search_candidates<T, false, ONE_CHUNK, COUNT, GREEDY, CONT, false, FEW>(
         p, tab, inst, smem, y, lane, g, bmin > 1 ? bmin : 1, tf0,
         bmin == 0 ? uni(sSL[0]) : inf_of<T>(), gpu, bestE, bestI, nf, ne);
     wave_argmin(bestE, bestI);
@@ -2914,6 +2934,21 @@ template <typename T> Grouped<T> to_grouped(const jdob_grouped_policy *o) {
   return g;
 }
 
+// Whether the grouping searches its groups' partition points as they come
+// (FEW): one or two, whose rows cost less than the bounds, and with the work
+// counters three, since the bounds' walk over (s, b) then also counts.  The
+// passes that count in its place hold WAVE / Jn batch sizes each: not where
+// they are many.  Measured, by the bounds or their walk -> as they come:
+// 20,000 x 12 users, 12 GPU levels, 2 layers 1.59 -> 0.98 ms and with counters
+// 2.13 -> 1.06, 3 layers with counters 1.56 -> 1.29, 8 layers 1.50 -> 3.24;
+// with counters 473 x 9 users, 50 GPU levels, binary (9 passes) 576 -> 437
+// us, 726 x 20 users, 70 GPU levels, binary (40 passes) 1.86 -> 2.15 ms.
+template <typename T> bool few_points(const Problem<T> &p, bool count, bool greedy) {
+  const int Jn = p.J - p.j_low, nb = WAVE / (Jn < WAVE ? Jn : WAVE);
+  const int passes = ((p.N - 1) / nb + 1) * ((Jn + WAVE - 1) / WAVE);
+  return p.s_end <= (count ? 3 : 2) && (!count || greedy || passes <= 32);
+}
+
 template <typename T>
 int launch_grouped(const jdob_problem *q, const jdob_grouped_policy *o, hipStream_t stream) {
   const Problem<T> p = to_problem<T>(q);
@@ -2924,20 +2959,28 @@ int launch_grouped(const jdob_problem *q, const jdob_grouped_policy *o, hipStrea
   const bool greedy = (q->mode & JDOB_MODE_GREEDY) != 0;
   const bool one = p.J - p.j_low <= WAVE;
   const bool count = g.ninner != nullptr || g.nfeas != nullptr || g.nevals != nullptr;
+  const bool few = few_points(p, count, greedy);
   const dim3 block(WAVE);
   const int64_t I = q->num_instances;
   for (int64_t first = 0; first < I; first += MAX_BLOCKS_PER_LAUNCH) {
     const int64_t n = (I - first < MAX_BLOCKS_PER_LAUNCH) ? I - first : MAX_BLOCKS_PER_LAUNCH;
     const dim3 grid((unsigned)n);
     const GroupedArgs<T> a{p, g, first};
-#define JDOB_LAUNCH(OC, CN, GR)                                                               \
+#define JDOB_LAUNCH_FEW(OC, CN, GR, CT)                                                       \
   do {                                                                                        \
-    if (p.cont)                                                                               \
-      hipLaunchKernelGGL((jdob_grouped_kernel<T, OC, CN, GR, true>), grid, block, lds, stream, \
-                         a);                                                                  \
-    else                                                                                      \
-      hipLaunchKernelGGL((jdob_grouped_kernel<T, OC, CN, GR, false>), grid, block, lds,        \
+    if (few)                                                                                  \
+      hipLaunchKernelGGL((jdob_grouped_kernel<T, OC, CN, GR, CT, true>), grid, block, lds,    \
                          stream, a);                                                          \
+    else                                                                                      \
+      hipLaunchKernelGGL((jdob_grouped_kernel<T, OC, CN, GR, CT, false>), grid, block, lds,   \
+                         stream, a);                                                          \
+  } while (0)
+#define JDOB_LAUNCH(OC, CN, GR)                  \
+  do {                                           \
+    if (p.cont)                                  \
+      JDOB_LAUNCH_FEW(OC, CN, GR, true);         \
+    else                                         \
+      JDOB_LAUNCH_FEW(OC, CN, GR, false);        \
   } while (0)
     if (greedy) {
       if (count) JDOB_LAUNCH(false, true, true);
@@ -2950,6 +2993,7 @@ int launch_grouped(const jdob_problem *q, const jdob_grouped_policy *o, hipStrea
       else JDOB_LAUNCH(false, false, false);
     }
 #undef JDOB_LAUNCH
+#undef JDOB_LAUNCH_FEW
     if (hipGetLastError() != hipSuccess) return JDOB_ERR_HIP;
   }
   return JDOB_OK;

@@ -41,6 +41,8 @@ for n, c in enumerate(json.loads(sys.stdin.read())):
         p[k] = float(p[k] * f) if np.isscalar(p[k]) else (p[k] * p[k].dtype.type(f)).astype(p[k].dtype)
     for k, v in c.get("fill", {}).items():
         p[k] = np.full_like(p[k], v)
+    if c.get("busy"):
+        p["t_free"] = (c["busy"] * p["deadline"].min(axis=1)).astype(p["t_free"].dtype)
     grouped = c.get("grouped", False)
     ora = oracle.solve_grouped(p, threads=4) if grouped else oracle.solve(p, threads=4)
     d = jdob.to_device(p, "cpu")
@@ -158,3 +160,14 @@ def test_rates_without_a_reciprocal(run, base):
     upload takes no time, and offloading is feasible."""
     run([dict(base=base, kw=dict(N=N, L=9, K=4, J=8), I=32, stream=7001, keep_mode=False, mode=mode,
               fill=dict(bits=0.0, rate=1e-40)) for N in (3, 8, 20) for mode in (0, 1, 8)])
+
+
+# one to four partition points, passes of several batch sizes, of one, and of two chunks of GPU levels
+@pytest.mark.parametrize("J", [1, 9, 33, 70])
+@pytest.mark.parametrize("L", [1, 2, 3, 4])
+def test_grouping_over_few_partition_points(run, L, J):
+    """Partition points searched as they come, with counting passes: winners
+    and counters are the oracle's, on an idle and on a busy GPU."""
+    run([dict(base=base, grouped=True, mode=mode, dtype=dtype, stream=8900 + n, kw=dict(N=N, L=L, K=5, J=J), busy=busy)
+         for base in ("g20", "p5") for mode in (0, 1, 2, 4) for n, (N, dtype, busy) in
+         enumerate(((2, "f32", 0.0), (7, "f32", 0.4), (6, "f64", 0.2)))])
