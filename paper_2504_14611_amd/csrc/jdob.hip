@@ -30,9 +30,9 @@
 //     bounds: partition points, batches and candidates whose bound exceeds
 //     the energy of local computing or of a candidate found before can
 //     neither win nor tie (see beaten).  Searched best bound first, few are
-//     left: 1,048,576 instances of 32 users, 22 layers 9.5 -> 1.02 ms, 65,537
-//     of 128 users, 50 layers 12.7 -> 0.94 ms, the grouping of 65,536
-//     instances of 10 users 22.7 -> 4.8 ms.
+//     left: 1,048,576 instances of 32 users, 22 layers 9.46 -> 1.05 ms, 65,537
+//     of 128 users, 50 layers 12.7 -> 0.95 ms, the grouping of 65,536
+//     instances of 10 users 22.7 -> 4.49 ms.
 // The kernel is a VALU/LDS-bound loop of compares, selects and adds: it is
 // not a dense contraction and uses no matrix cores.
 
@@ -109,8 +109,13 @@ struct Layout {
 constexpr int QCAP = 2 * WAVE;
 
 // Whether the grid search with CPU levels queues those candidates: from 17
-// users up (measured: c2 with 16 users 0.86 ms walking, 0.95 ms queued; c3
-// with 32 users 11.1 ms walking, 10.8 ms queued, before other changes).
+// users up.  Since bounds leave few of them, the queue seldom pays (its 512
+// bytes of LDS cost resident instances), but walking costs most where they are
+// many.  32,768 instances of 22 layers, 16 CPU levels, queued and walking:
+// some users gain by offloading, 64 users, 32 GPU levels 64.1 and 79.1 us, 48
+// users 59.2 and 62.0, 17 to 32 users, 8 GPU levels 61.3 to 54.3 and 59.0 to
+// 53.0; no local computing, 96 users, 8 GPU levels 203 and 180; elsewhere
+// within 2 %.
 __host__ __device__ inline bool queued_search(int N, bool cont, bool greedy) {
   return N > 16 && !cont && !greedy;
 }
@@ -578,9 +583,10 @@ template <typename T> __device__ inline bool one_per_lane(const Problem<T> &p) {
 // 64 layers (one_per_lane), of the fused or the joint call: the rows are loaded
 // together and kept in registers, the sums run along the lanes, and with local
 // computing feasible the partition points that cannot beat it drop out before
-// anything else is computed.  (1,048,576 instances of 32 users, 22 layers, most of which end
-// there: 1.57 -> 1.02 ms; 65,536 by the joint call 155 -> 100 us; 200,003 of them, greedy, 298 -> 202 us; 4,096 of 8
-// users, 16 layers, where one wave's latency is the time, 22.3 -> 19.5 us.)
+// anything else is computed.  (1,048,576 instances of 32 users, 22 layers, most
+// of which end there: 1.57 -> 1.05 ms; 65,536 by the joint call 155 -> 100 us; 200,003 of
+// them, greedy, 298 -> 198 us; 4,096 of 8 users, 16 layers, with counters, where
+// one wave's latency is the time, 22.3 -> 18.9 us.)
 template <typename T, bool FROM_TABLES, bool CONT, bool KEEP>
 __device__ bool prepare_lanes(const Problem<T> &p, const Tables<T> &tab, int64_t inst,
                               unsigned char *smem, const Layout &y, int lane, T tfree,
@@ -769,9 +775,9 @@ __device__ bool prepare_lanes(const Problem<T> &p, const Tables<T> &tab, int64_t
   return true;
 }
 
-// Preparation of the fused solve.  Every step is exact (orders, minima and
-// the tests of the contract), so the candidate search only runs where it can
-// find something:
+// Preparation of the fused solve.  Orders, minima and the tests of the contract
+// are exact, and what is dropped by an energy bound is dropped with its margin
+// (see beaten), so the candidate search only runs where it can find something:
 //   1. the rows, the level tables, the sums C, A, B, and each user's local
 //      level and energy against its own deadline (constraint (8), Eq. (20));
 //   2. without sorting the users: bmin, from the last user of pi that has no
@@ -1627,9 +1633,11 @@ __device__ inline void search_candidates(const Problem<T> &p, const Tables<T> &t
   }
 
   // Partition points by their lowest bound, until it is beaten by the best
-  // energy found: the winner's is usually among the first (10 users in a
-  // group: 22 partition points hold feasible candidates, 1.3 are searched; 32
-  // users: 13 and 0.1; 128 users: 14 and 6).  A partition point's bound is the
+  // energy found: the winner's is usually among the first (grouping of 10
+  // users, 22 layers: in a group's search 21.5 partition points hold feasible
+  // candidates, 0.8 are searched; 128 users, 50 layers: 13.3 and 4.9; 10 users,
+  // continuous, all better off offloading: 4.7 and 2.1).  A partition point's
+  // bound is the
   // least over b of: the least GPU energy, the upload energy of the first b
   // users, the local energy of the others, and b users' CPU energy at the
   // lowest frequency that the first user, whose budget is the largest, can run
@@ -2082,8 +2090,9 @@ __device__ inline void group_winner(const Problem<T> &p, int64_t inst, unsigned 
 // program's state and the inner search want more than 64 registers; at seven
 // waves a few values still spill, outside the pass loops, but the short
 // searches of small groups wait on LDS, and resident waves hide that
-// (measured: 65,536 instances of 10 users 5.15 ms at eight and seven waves,
-// 5.39 at six and five; 4,239 of 6 users 389, 380, 369 and 369 us).
+// (measured at eight, seven, six and five waves: 65,536 instances of 10 users
+// 5.22, 5.06, 5.22 and 5.19 ms; 16,384 of 20 users 6.83, 6.41, 6.21 and 6.26;
+// 4,239 of 6 users 430, 406, 393 and 393 us).  FEW: see few_points.
 template <typename T, bool ONE_CHUNK, bool COUNT, bool GREEDY, bool CONT, bool FEW>
 __global__ __launch_bounds__(WAVE, 7) void jdob_grouped_kernel(GroupedArgs<T> args) {
   extern __shared__ __align__(16) unsigned char smem[];

@@ -336,7 +336,7 @@ template <typename T> struct GpuCost {
       T v = inf_of<T>();
       for (int j = 0; j < n; ++j) {
         const T e = P[j] * r[j];
-        v = (ab * r[j] <= some) & (e < v) ? e : v;
+        v = ((ab * r[j] <= some) & (e < v)) ? e : v;
       }
       return v < inf_of<T>() ? ab * v : T(0);  // (no level: infeasible)
     }

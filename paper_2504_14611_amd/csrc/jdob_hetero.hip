@@ -430,7 +430,7 @@ __device__ inline int feasible_levels(const HProblem<T> &p, const T *sr, T lo, T
 // batch of its own, which no larger batch lets it go below; feasibility
 // falls with b and rises with j, so the test is that of the top GPU level.
 // (16 users, 22 layers: 5.5 of 21.5 partition points with feasible candidates
-// are then searched, best bound first; 13 of the batches of 72 passes.)
+// are then searched, best bound first, in 7.7 passes of 72.)
 // Counts the feasible candidates into nfeas, nevals when COUNT.  (Inlined: as
 // a function it kept its arguments in 1 KB of scratch a lane; grouping of 531 x
 // 21 users, binary64: 47 ms, 62 as a function.)
@@ -843,9 +843,11 @@ __device__ void hsearch(const HProblem<T> &p, int64_t inst, unsigned char *smem,
   // the bounds do not pay: with one or two partition points, and with more
   // users than let the bounds take several at once (in the greedy search,
   // whose rows cost less, than four) unless the orders are at hand.  Measured
-  // on the continuous frequency: 25,078 x 17 users 183 us as they come, 130 by
-  // bounds; 6,453 x 47 users, greedy, 208 and 273; 1,769 x 18, greedy, 70 and
-  // 85.  Nor where the greedy search counts, for which every partition point is
+  // with CPU levels, 16,384 instances, 22 layers, 8 GPU levels: 33 users 375 us
+  // as they come, 490 by bounds, 64 users 633 and 832, 32 users 325 and 309; on
+  // the continuous frequency: 25,078 x 17 users 183 us as they come,
+  // 130 by bounds; 16,384 x 17 users, 22 layers 232 and 251; 6,453 x 47 users,
+  // greedy, 208 and 273; 1,769 x 18, greedy, 70 and 85.  Nor where the greedy search counts, for which every partition point is
   // searched: grouping of 600 x 11 users 5.23 ms by bounds, 4.37 as they come.
   if ((GREEDY && COUNT) || s_end <= 2 || !(N <= 16 || (!GREEDY && N <= 32) || y.tab >= 0)) {
     for (int s = 0; s < s_end; ++s) search_point(std::false_type{}, s);
@@ -978,7 +980,7 @@ __device__ void hwinner(const HProblem<T> &p, int64_t inst, unsigned char *smem,
 }
 
 // Eight waves per SIMD: the rows and the bounds wait on LDS (262,144 x 16
-// users, 22 layers: 1.87 ms at eight waves, 1.92 at seven, 2.00 at six; 5.34
+// users, 22 layers: 1.83 ms at eight waves, 1.85 at seven, 1.96 at six; 5.34
 // before the bounds).  LG > 0: level rows of 2^LG
 // entries (launches without the work counters).
 template <typename T, bool COUNT, bool GREEDY, bool CONT, int LG = 0>
@@ -1065,9 +1067,8 @@ __global__ __launch_bounds__(WAVE, 8) void jdob_hetero_kernel(HArgs<T> args) {
 // dynamic program keeps, per prefix of the deadline order, the front of
 // non-dominated (total energy, GPU release time) states, as the other
 // grouping kernel does.  Six waves per SIMD: at more, values spill
-// to scratch (16,384 x 10 users, continuous, before the bound of the GPU energy
-// knew the batch's time: 5.19 ms at six waves, 5.43 at seven, 5.75 at eight,
-// 5.56 at five; 3.25 ms now, 9.3 before the bounds).
+// to scratch (16,384 x 10 users, continuous: 3.25 ms at six waves, 3.32 at
+// seven, 3.59 at eight, 3.44 at five; 9.4 before the bounds).
 template <typename T, bool COUNT, bool GREEDY, bool CONT>
 __global__ __launch_bounds__(WAVE, 6) void jdob_hetero_grouped_kernel(HGArgs<T> args) {
   extern __shared__ __align__(16) unsigned char smem[];

@@ -49,6 +49,10 @@ def both(prob, call):
     return out
 
 
+def joint(d, **kw):
+    return jdob.eval_joint(d, jdob.eval_user_tables(d), **kw)
+
+
 def problem(base, n, mode, busy, dtype, seed, **kw):
     p = W.generate(W.WORKLOADS[base].replace(name="bounds", stream=seed, num_instances=n, dtype=dtype, **kw))
     p["mode"] = int(p["mode"]) | mode
@@ -130,3 +134,52 @@ def test_bounds_hetero_grouped(base, n, kw, mode):
     ora = oracle.solve_grouped(prob, threads=16)
     for gpu in both(prob, jdob.solve_grouped):
         compare_grouped(prob, gpu, ora, label)
+
+
+# Two to four GPU levels are tried one by one in the bound of the GPU energy,
+# from five on it takes the frequency at which a second of work costs least:
+# with neither kind of power (at the lowest level, at the highest) and with that
+# frequency below and above the levels.
+POWERS = [dict(), dict(gpu_p_static=0.0), dict(gpu_c=0.0), dict(gpu_p_static=1e-4), dict(gpu_p_static=1e4)]
+
+
+@pytest.mark.parametrize("power", range(len(POWERS)))
+@pytest.mark.parametrize("base,n,kw", [("p4a", 64, dict(N=10, L=16)), ("p4b", 64, dict(N=7, L=9)),
+                                       ("c4b", 32, dict(N=40, L=22, K=8))])
+def test_bounds_gpu_levels(base, n, kw, power):
+    for J in (2, 3, 4, 5, 16):
+        prob = problem(base, n, 0, J == 3, "f32", 8500 + J, J=J, **kw)
+        for k, f in POWERS[power].items():
+            prob[k] = float(prob[k] * f)
+        label = f"bounds {base} {kw} J={J} {POWERS[power]}"
+        print(f"[gpu] {label}", flush=True)
+        ora = oracle.solve(prob, threads=16)
+        for gpu in both(prob, jdob.solve_batch) + both(prob, joint):
+            compare(prob, gpu, ora, label=label)
+
+
+# the shortest rows of an instance, whose preparation keeps values in the room of the batch records
+@pytest.mark.parametrize("J", [2, 16, 32, 64])
+def test_bounds_few_users(J):
+    for N in (1, 2, 3, 5, 9, 12):
+        for mode, dtype in ((0, "f32"), (0, "f64"), (1, "f32"), (8, "f32")):
+            prob = problem("c2b", 96, mode, False, dtype, 8600 + N, N=N, L=6, K=8, J=J)
+            label = f"bounds few users N={N} J={J} mode={prob['mode']} {dtype}"
+            print(f"[gpu] {label}", flush=True)
+            ora = oracle.solve(prob, threads=16)
+            for gpu in both(prob, jdob.solve_batch) + both(prob, joint):
+                compare(prob, gpu, ora, label=label)
+
+
+# one to four partition points, searched as they come where they are few, with
+# counting passes, and by bounds where they or their passes are many
+@pytest.mark.parametrize("mode", [0, 1, 4, 8])
+@pytest.mark.parametrize("L", [1, 2, 3, 4])
+def test_bounds_grouped_over_few_partition_points(L, mode):
+    for n, N, J, dtype in ((48, 2, 1, "f32"), (48, 7, 9, "f32"), (32, 6, 33, "f64"), (16, 20, 70, "f32")):
+        prob = problem("g20" if mode != 8 else "p5", n, mode, N == 7, dtype, 8700 + N, N=N, L=L, K=2 if mode == 8 else 8, J=J)
+        label = f"bounds grouped N={N} L={L} J={J} mode={prob['mode']} {dtype}"
+        print(f"[gpu] {label}", flush=True)
+        ora = oracle.solve_grouped(prob, threads=16)
+        for gpu in both(prob, jdob.solve_grouped):
+            compare_grouped(prob, gpu, ora, label)

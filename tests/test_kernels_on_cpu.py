@@ -171,3 +171,12 @@ def test_grouping_over_few_partition_points(run, L, J):
     run([dict(base=base, grouped=True, mode=mode, dtype=dtype, stream=8900 + n, kw=dict(N=N, L=L, K=5, J=J), busy=busy)
          for base in ("g20", "p5") for mode in (0, 1, 2, 4) for n, (N, dtype, busy) in
          enumerate(((2, "f32", 0.0), (7, "f32", 0.4), (6, "f64", 0.2)))])
+
+
+@pytest.mark.parametrize("J", [2, 3, 4, 5, 16])
+def test_gpu_power_at_the_ends(run, J):
+    """The bound of the GPU energy without static or dynamic power, and with
+    the cheapest frequency below and above the levels."""
+    run([dict(base=base, kw=dict(N=N, L=9, J=J), I=4, scale=scale, stream=8950)
+         for base, N in (("p4a", 10), ("p4b", 70), ("h2", 9)) for scale in
+         (dict(gpu_p_static=0.0), dict(gpu_c=0.0), dict(gpu_p_static=1e-4), dict(gpu_p_static=1e4))])
