@@ -518,8 +518,10 @@ def main():
         kernel = (f"{kfamily}<{T},false,{gr},{ct},{lg}>" if not grouped else
                   f"{kfamily}<{T},false,{gr},{ct}>")
     elif grouped:
-        kernel = (f"jdob_grouped_kernel<{T},false,false,true,{ct}>" if mode & 1 else
-                  f"jdob_grouped_kernel<{T},{one},false,false,{ct}>")
+        # one or two partition points are searched as they come (the launch's own rule)
+        few = "true" if (1 if mode & 4 else w.L) <= 2 else "false"
+        kernel = (f"jdob_grouped_kernel<{T},false,false,true,{ct},{few}>" if mode & 1 else
+                  f"jdob_grouped_kernel<{T},{one},false,false,{ct},{few}>")
     else:
         # queued evaluation of multi-level candidates from 17 users up (the
         # launch's own rule for the grid with CPU levels)

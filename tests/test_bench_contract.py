@@ -110,3 +110,21 @@ def test_stage1_kernel_choice():
     assert bench.tables_kernel_name(w) == "jdob_tables_kernel<float, true, 4>"
     w = W.WORKLOADS["c3"].replace(N=10)  # (L+1)*N = 230: not four-entry rows of one point
     assert bench.tables_kernel_name(w) == "jdob_tables_kernel<float, false, -1>"
+
+
+def test_counter_summaries_are_found_and_whole(monkeypatch):
+    """The counter summaries under profiles/ are where the bench line looks
+    for them and hold every figure that it reports, while the kernel source is
+    the one they were taken on, and nothing when it is another."""
+    tags = {"jdob_solve_kernel": ("c2", "c3", "c3_greedy", "c4", "c4b", "p4a", "p4b"), "jdob_hetero_kernel": ("h1", "h2"),
+            "jdob_grouped_kernel": ("g10", "g20", "p5"), "jdob_hetero_grouped_kernel": ("h5",)}
+    for kernel, names in tags.items():
+        for tag in names:
+            path = os.path.join(ROOT, "profiles", f"{kernel}_{tag}_traffic.txt")
+            (source,) = [ln.split("=")[1].strip() for ln in open(path) if ln.startswith("source_sha256_16")]
+            monkeypatch.setattr(bench, "source_hash", lambda: source)
+            got = bench.measured_counters(kernel, tag)
+            assert got["traffic"] > 0 and all(v is not None for v in got["valu"].values()), (kernel, tag)
+            assert 0 < got["valu"]["busy"] <= 1
+            monkeypatch.setattr(bench, "source_hash", lambda: "another")
+            assert bench.measured_counters(kernel, tag) == {}
