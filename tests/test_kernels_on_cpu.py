@@ -94,13 +94,12 @@ def run(tmp_path_factory):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
-@pytest.mark.parametrize("mode", [0, 1, 2, 8])
-def test_few_users_stay_in_the_launch(run, mode, dtype):
+def test_few_users_stay_in_the_launch(run, dtype):
     """The rows of few users are the shortest: at 1 to 17 users and GPU levels
     on both sides of every count of batch records."""
-    run([dict(base=base, mode=mode, dtype=dtype, kw=dict(N=N, L=1 + N % 4, K=4, J=J))
-         for N in (1, 2, 3, 4, 5, 6, 9, 10, 12, 13, 16, 17)
-         for J in (1, 2, 5, 8, 16, 31, 33, 48, 64, 65) for base in ("c2",)])
+    run([dict(base="c2", mode=mode, dtype=dtype, kw=dict(N=N, L=1 + N % 4, K=4, J=J))
+         for mode in (0, 1, 2, 8) for N in (1, 2, 3, 4, 5, 6, 9, 10, 12, 13, 16, 17)
+         for J in (1, 2, 5, 8, 16, 31, 33, 48, 64, 65)])
 
 
 SHAPES = [dict(base="p4a", kw=dict(N=10, L=22, K=4, J=32)), dict(base="c2b", kw=dict(N=20, L=22, K=8, J=9)),
@@ -111,9 +110,8 @@ SHAPES = [dict(base="p4a", kw=dict(N=10, L=22, K=4, J=32)), dict(base="c2b", kw=
           dict(base="p5", grouped=True, kw=dict(N=5, L=3, J=33))]
 
 
-@pytest.mark.parametrize("k", range(len(SHAPES)))
-def test_shapes(run, k):
-    run([dict(SHAPES[k], mode=mode, dtype=dtype) for mode in (0, 1, 2, 4) for dtype in ("f32", "f64")])
+def test_shapes(run):
+    run([dict(s, mode=mode, dtype=dtype) for s in SHAPES for mode in (0, 1, 2, 4) for dtype in ("f32", "f64")])
 
 
 HETERO = [dict(base="h1", kw=dict(N=12, L=6, K=5, J=9)), dict(base="h1", kw=dict(N=16, L=66, K=3, J=4)),
@@ -122,61 +120,56 @@ HETERO = [dict(base="h1", kw=dict(N=12, L=6, K=5, J=9)), dict(base="h1", kw=dict
           dict(base="h1", grouped=True, I=1, kw=dict(N=10, L=60, K=5, J=8))]
 
 
-@pytest.mark.parametrize("k", range(len(HETERO)))
-def test_heterogeneous_users(run, k):
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_heterogeneous_users(run, dtype):
     """Several partition points' gamma orders are formed in one room: keys,
     then records."""
-    run([dict(HETERO[k], mode=mode, dtype=dtype) for mode in (0, 1, 4, 8) for dtype in ("f32", "f64")])
+    run([dict(h, mode=mode, dtype=dtype) for h in HETERO for mode in (0, 1, 4, 8)])
 
 
-QUEUED = [dict(base="c4b", kw=dict(N=33, L=9, K=8, J=16)), dict(base="c4b", kw=dict(N=100, L=22, K=8, J=64)),
+QUEUED = [dict(base="c4b", kw=dict(N=33, L=9, K=8, J=16)), dict(base="c4b", kw=dict(N=100, L=22, K=8, J=64), I=1),
           dict(base="c2b", kw=dict(N=33, L=9, K=8, J=8)), dict(base="c2b", kw=dict(N=20, L=22, K=16, J=65)),
           dict(base="c2b", kw=dict(N=70, L=9, K=8, J=16))]
 
 
-@pytest.mark.parametrize("k", range(len(QUEUED)))
-def test_queue_of_candidates(run, k):
+def test_queue_of_candidates(run):
     """A full queue of candidates is evaluated in the pass that filled it.
     (Cheap uploads and GPU levels leave many candidates to evaluate.)"""
-    run([dict(QUEUED[k], dtype=dtype, mode=0, stream=8700 + n, scale=dict(deadline=a, p_tx=b, gpu_c=b, gpu_p_static=b))
-         for dtype in ("f32", "f64") for n in range(3) for a in (0.7, 1.0, 1.5) for b in (0.01, 0.1)])
+    run([dict(q, dtype=dtype, mode=0, stream=8700 + n, scale=dict(deadline=a, p_tx=b, gpu_c=b, gpu_p_static=b))
+         for q in QUEUED for dtype in ("f32", "f64") for n in range(3) for a in (0.7, 1.0, 1.5) for b in (0.01, 0.1)])
 
 
-@pytest.mark.parametrize("kw", [dict(N=7, L=8, K=5, J=5), dict(N=20, L=6, K=4, J=12), dict(N=40, L=5, K=3, J=4)])
-@pytest.mark.parametrize("base", ["h1", "h2"])
-def test_heterogeneous_energies_that_overflow(run, base, kw):
+def test_heterogeneous_energies_that_overflow(run):
     """Frequencies whose squares are past binary32 make energies infinite.
     Feasibility and the counters do not depend on them, and with none finite
     the first candidate of the order wins.  (Instances whose energy is no
     number, infinity times no work, are left out.)"""
     run([dict(base=base, mode=mode, kw=kw, I=12, stream=8800 + f, keep_mode=False, overflow=True,
               scale=dict(cycles=f * 1e9, user_local_freq=f * 1e9, local_freq=f * 1e9, user_kappa=1e-8, kappa=1e-8))
+         for base in ("h1", "h2") for kw in (dict(N=7, L=8, K=5, J=5), dict(N=20, L=6, K=4, J=12), dict(N=40, L=5, K=3, J=4))
          for mode in (0, 1, 2) for f in (5, 10, 12, 16)])
 
 
-@pytest.mark.parametrize("base", ["c2b", "p4b"])
-def test_rates_without_a_reciprocal(run, base):
+def test_rates_without_a_reciprocal(run):
     """Nothing to upload over links whose rates are denormal numbers: the
     upload takes no time, and offloading is feasible."""
     run([dict(base=base, kw=dict(N=N, L=9, K=4, J=8), I=32, stream=7001, keep_mode=False, mode=mode,
-              fill=dict(bits=0.0, rate=1e-40)) for N in (3, 8, 20) for mode in (0, 1, 8)])
+              fill=dict(bits=0.0, rate=1e-40)) for base in ("c2b", "p4b") for N in (3, 8, 20) for mode in (0, 1, 8)])
 
 
-# one to four partition points, passes of several batch sizes, of one, and of two chunks of GPU levels
-@pytest.mark.parametrize("J", [1, 9, 33, 70])
 @pytest.mark.parametrize("L", [1, 2, 3, 4])
-def test_grouping_over_few_partition_points(run, L, J):
+def test_grouping_over_few_partition_points(run, L):
     """Partition points searched as they come, with counting passes: winners
-    and counters are the oracle's, on an idle and on a busy GPU."""
+    and counters are the oracle's, on an idle and on a busy GPU.  Passes of
+    several batch sizes, of one, and of two chunks of GPU levels."""
     run([dict(base=base, grouped=True, mode=mode, dtype=dtype, stream=8900 + n, kw=dict(N=N, L=L, K=5, J=J), busy=busy)
-         for base in ("g20", "p5") for mode in (0, 1, 2, 4) for n, (N, dtype, busy) in
+         for base in ("g20", "p5") for mode in (0, 1, 2, 4) for J in (1, 9, 33, 70) for n, (N, dtype, busy) in
          enumerate(((2, "f32", 0.0), (7, "f32", 0.4), (6, "f64", 0.2)))])
 
 
-@pytest.mark.parametrize("J", [2, 3, 4, 5, 16])
-def test_gpu_power_at_the_ends(run, J):
+def test_gpu_power_at_the_ends(run):
     """The bound of the GPU energy without static or dynamic power, and with
     the cheapest frequency below and above the levels."""
     run([dict(base=base, kw=dict(N=N, L=9, J=J), I=4, scale=scale, stream=8950)
-         for base, N in (("p4a", 10), ("p4b", 70), ("h2", 9)) for scale in
+         for J in (2, 3, 4, 5, 16) for base, N in (("p4a", 10), ("p4b", 70), ("h2", 9)) for scale in
          (dict(gpu_p_static=0.0), dict(gpu_c=0.0), dict(gpu_p_static=1e-4), dict(gpu_p_static=1e4))])
