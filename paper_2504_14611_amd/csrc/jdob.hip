@@ -2090,9 +2090,10 @@ __device__ inline void group_winner(const Problem<T> &p, int64_t inst, unsigned 
 // program's state and the inner search want more than 64 registers; at seven
 // waves a few values still spill, outside the pass loops, but the short
 // searches of small groups wait on LDS, and resident waves hide that
-// (measured at eight, seven, six and five waves: 65,536 instances of 10 users
-// 5.22, 5.06, 5.22 and 5.19 ms; 16,384 of 20 users 6.83, 6.41, 6.21 and 6.26;
-// 4,239 of 6 users 430, 406, 393 and 393 us).  FEW: see few_points.
+// (measured at eight, seven, six and five waves, 22 layers: 65,536 instances of
+// 10 users, 8 CPU and 16 GPU levels 5.22, 5.06, 5.22 and 5.19 ms; 16,384 of 20
+// users, 16 and 32 levels 6.83, 6.41, 6.21 and 6.26; 4,239 of 6 users, 8 and 16
+// levels 430, 406, 393 and 393 us).  FEW: see few_points.
 template <typename T, bool ONE_CHUNK, bool COUNT, bool GREEDY, bool CONT, bool FEW>
 __global__ __launch_bounds__(WAVE, 7) void jdob_grouped_kernel(GroupedArgs<T> args) {
   extern __shared__ __align__(16) unsigned char smem[];
